@@ -20,7 +20,7 @@ OBJDIR = os.path.join(PKG, "_build")
 
 SOURCES = ["rrs_api.cpp", "rrs_quant.hip", "rrs_weight.hip", "rrs_gemm.hip", "rrs_gemm_small.hip",
            "rrs_gemm_decode.hip", "rrs_quant_wave.hip", "rrs_reorder.hip", "rrs_quant_rows.hip",
-           "rrs_gemm_stream.hip", "rrs_gemm_stream_gather.hip", "rrs_noalloc.hip"]
+           "rrs_gemm_stream.hip", "rrs_gemm_stream_gather.hip", "rrs_gemm_mid.hip", "rrs_noalloc.hip"]
 
 # Per-source code-generation options on top of COMMON.
 # rrs_gemm_stream_gather.hip: keep MFMA results in VGPRs (the per-block

@@ -458,6 +458,9 @@ hipError_t launch_w4a4_gemm(const uint8_t* Xq, const float* a_scale, const float
   if (decode_kernel_fits(M))
     return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
                                    stream, nullptr, lay);
+  if (mid_kernel_fits(M, N))
+    return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, nullptr, M, N, K, g, Y,
+                                out_scale, stream, lay);
   if (!main_kernel_fits(K, g))
     return launch_w4a4_gemm_small(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
                                   stream, lay);
@@ -469,6 +472,11 @@ hipError_t launch_w4a4_gemm_per_channel(const uint8_t* Xq, const float* a_scale,
                                        const uint8_t* Wq, const float* w_scale, int M, int N,
                                        int K, uint16_t* Y, float out_scale, hipStream_t stream,
                                        WqLayout lay) {
+  // Up to 16 tokens too: this scheme has no few-token kernel of its own, and the
+  // main kernel's 256-row tiles took 35 us at K = N = 4096 whatever M is.
+  if (M <= 16 || mid_kernel_fits(M, N))
+    return launch_w4a4_gemm_mid_per_channel(Xq, a_scale, Wq, w_scale, M, N, K, Y, out_scale,
+                                            stream, lay);
   if (!main_kernel_fits(K, 128))
     return launch_w4a4_gemm_scheme(1, Xq, a_scale, nullptr, Wq, w_scale, M, N, K, K, Y,
                                    out_scale, stream, lay);
@@ -495,6 +503,9 @@ hipError_t launch_w4a4_gemm_reorder(const uint8_t* Xq, const float* a_scale,
   if (decode_gather_fits(M))
     return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
                                    stream, border, lay);
+  if (mid_kernel_fits(M, N))
+    return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g, Y,
+                                out_scale, stream, lay);
   // Every shape the ABI accepts fits the main kernel (K / 32 >= 16 is a power
   // of two); the fallback kernel has no gather.
   if (!main_kernel_fits(K, g)) return hipErrorInvalidValue;
@@ -510,6 +521,8 @@ hipError_t launch_w4a4_gemm_partials(const uint8_t* Xq, const uint8_t* Wq, int M
     return launch_w4a4_gemm_stream_partials(Xq, Wq, M, N, K, g, P, stream, lay);
   if (decode_kernel_fits(M) && !lay.tiled)
     return launch_w4a4_gemm_decode_partials(Xq, Wq, M, N, K, g, P, stream);
+  if (mid_kernel_fits(M, N) && !lay.tiled)
+    return launch_w4a4_gemm_mid_partials(Xq, Wq, M, N, K, g, P, stream);
   if (!main_kernel_fits(K, g))
     return launch_w4a4_gemm_partials_small(Xq, Wq, M, N, K, g, P, stream, lay);
   return launch_main<true>(Xq, nullptr, nullptr, Wq, nullptr, M, N, K, g, nullptr, P, 0.0f,

@@ -120,8 +120,8 @@ hipError_t launch_w4a4_gemm_partials_small(const uint8_t* Xq, const uint8_t* Wq,
                                            int N, int K, int g, int32_t* P,
                                            hipStream_t stream, WqLayout lay = {false});
 
-// Few-token kernel (decode): streams Wq once, for M <= 64 (up to four blocks
-// of 16 tokens); its runtime-reorder variant takes M <= 16.
+// Few-token kernel (decode): streams Wq once, for M <= 16, with or without the
+// runtime reorder.
 bool decode_kernel_fits(int M);
 bool decode_gather_fits(int M);
 // Runtime-reorder GEMM on the weight stream (rrs_gemm_stream.hip): up to 16
@@ -141,11 +141,24 @@ hipError_t launch_w4a4_gemm_decode(const uint8_t* Xq, const float* a_scale,
 hipError_t launch_w4a4_gemm_decode_partials(const uint8_t* Xq, const uint8_t* Wq, int M, int N,
                                             int K, int g, int32_t* P, hipStream_t stream);
 
+// 17 to a few hundred tokens (rrs_gemm_mid.hip): small tiles whose waves split
+// K. mid_kernel_fits says where it beats the main kernel; it takes any M.
+bool mid_kernel_fits(int M, int N);
+hipError_t launch_w4a4_gemm_mid(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                                const uint8_t* Wq, const float* w_scale, const int32_t* border,
+                                int M, int N, int K, int g, uint16_t* Y, float out_scale,
+                                hipStream_t stream, WqLayout lay);
+hipError_t launch_w4a4_gemm_mid_per_channel(const uint8_t* Xq, const float* a_scale,
+                                            const uint8_t* Wq, const float* w_scale, int M, int N,
+                                            int K, uint16_t* Y, float out_scale,
+                                            hipStream_t stream, WqLayout lay);
+hipError_t launch_w4a4_gemm_mid_partials(const uint8_t* Xq, const uint8_t* Wq, int M, int N, int K,
+                                         int g, int32_t* P, hipStream_t stream);
+
 // Weight-streaming kernel for few tokens (rrs_gemm_stream.hip): each
 // workgroup copies 16 whole rows of Wq into LDS with direct-to-LDS loads.
-// Up to 16 tokens: four waves, K >= 4 g (not K = 16384 with g <= 128). 17 to
-// 32 tokens at K = 8192: eight waves and two blocks of 16 tokens. Both
-// layouts, bit-identical results.
+// Up to 16 tokens, K >= 4 g (not K = 16384 with g <= 128). Both layouts,
+// bit-identical results.
 bool stream_kernel_fits(int M, int K, int g);
 hipError_t launch_w4a4_gemm_stream(const uint8_t* Xq, const float* a_scale,
                                    const float* s_group, const uint8_t* Wq,
