@@ -488,6 +488,43 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
                               int N, int K, int group_size, int flags, void* Y, void* workspace,
                               size_t workspace_bytes, void* stream);
 
+/*
+ * ------------------------------------------------------------------------
+ * GEMM on scratch memory. For many tokens the product runs faster when the
+ * token codes can first be written out in the matrix instruction's operand
+ * order (0.82 bytes per code). The functions below are the ones of the same
+ * names without "_scratch" plus a scratch buffer for that: same arguments,
+ * checks and results (Y bit for bit). scratch may be NULL or smaller than
+ * rrs_gemm_scratch_bytes: the call then runs as the plain function does. It
+ * must be 16-byte aligned, its contents before and after are undefined, and
+ * calls that may overlap need a scratch buffer each.
+ * ------------------------------------------------------------------------
+ */
+
+/* Scratch bytes with which the GEMM of this shape runs faster; 0 when none are
+ * used (few tokens, or invalid arguments). Any group size and flags. */
+size_t rrs_gemm_scratch_bytes(int M, int N, int K);
+
+/* rrs_w4a4_gemm_ex; with block_order rrs_w4a4_gemm_reorder; with s_group NULL
+ * (then block_order too, and group_size ignored) rrs_w4a4_gemm_per_channel. */
+rrs_status rrs_w4a4_gemm_scratch(const void* Xq, const float* a_scale, const float* s_group,
+                                 const void* Wq, const float* w_scale,
+                                 const int32_t* block_order, int M, int N, int K,
+                                 int group_size, int flags, void* Y, void* scratch,
+                                 size_t scratch_bytes, void* stream);
+
+/* rrs_linear_ex. */
+rrs_status rrs_linear_scratch(const void* X, const void* Wq, const float* w_scale, int M, int N,
+                              int K, int group_size, const int32_t* perm, int flags, void* Y,
+                              void* workspace, size_t workspace_bytes, void* scratch,
+                              size_t scratch_bytes, void* stream);
+
+/* rrs_linear_reorder. */
+rrs_status rrs_linear_reorder_scratch(const void* X, const void* Wq, const float* w_scale, int M,
+                                      int N, int K, int group_size, int flags, void* Y,
+                                      void* workspace, size_t workspace_bytes, void* scratch,
+                                      size_t scratch_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -53,6 +53,13 @@ _SIGNATURES = {
                               [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp]),
     "rrs_linear_reorder": (ctypes.c_int32,
                            [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _sz, _vp]),
+    "rrs_gemm_scratch_bytes": (_sz, [_i, _i, _i]),
+    "rrs_w4a4_gemm_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i,
+                                               _vp, _vp, _sz, _vp]),
+    "rrs_linear_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _i, _i, _i, _i, _vp, _i, _vp, _vp, _sz,
+                                            _vp, _sz, _vp]),
+    "rrs_linear_reorder_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp,
+                                                    _sz, _vp, _sz, _vp]),
 }
 
 # Channels per block of the runtime reorder (include/rrs.h, RRS_REORDER_BLOCK).
@@ -135,6 +142,17 @@ def _dev(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Tuple[int, ...])
     return t.data_ptr()
 
 
+def _gemm_scratch(M: int, N: int, K: int, device: torch.device):
+    """Scratch of the many-token GEMM as (tensor, pointer, bytes), from torch's caching
+    allocator on the current stream (which the call's launches use too, so the memory is
+    not handed out again before they ran); (None, None, 0) for few tokens."""
+    nbytes = lib().rrs_gemm_scratch_bytes(M, N, K) if M > 16 else 0
+    if nbytes == 0:
+        return None, None, 0
+    t = torch.empty((nbytes,), dtype=torch.uint8, device=device)
+    return t, t.data_ptr(), nbytes
+
+
 def _perm_ptr(perm: Optional[torch.Tensor], K: int) -> Optional[int]:
     if perm is None:
         return None
@@ -190,8 +208,9 @@ def w4a4_gemm(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Tensor,
             _dev(Wq, "Wq", torch.uint8, (N, Kh)), _dev(w_scale, "w_scale", torch.float32, (N,)))
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    _check(lib().rrs_w4a4_gemm_ex(*args, M, N, K, g, flags, yp, _stream(Xq.device)),
-           "rrs_w4a4_gemm")
+    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    _check(lib().rrs_w4a4_gemm_scratch(*args, None, M, N, K, g, flags, yp, sp, sb,
+                                       _stream(Xq.device)), "rrs_w4a4_gemm")
     return Y
 
 
@@ -209,9 +228,11 @@ def linear(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    _check(lib().rrs_linear_ex(xp, wqp, wsp, M, N, K, g, _perm_ptr(perm, K), flags, yp,
-                               workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                               _stream(X.device)), "rrs_linear")
+    keep, sp, sb = _gemm_scratch(M, N, K, X.device)
+    _check(lib().rrs_linear_scratch(xp, wqp, wsp, M, N, K, g, _perm_ptr(perm, K), flags, yp,
+                                    workspace.data_ptr(),
+                                    workspace.numel() * workspace.element_size(), sp, sb,
+                                    _stream(X.device)), "rrs_linear")
     return Y
 
 
@@ -360,8 +381,9 @@ def w4a4_gemm_per_channel(Xq: torch.Tensor, a_scale: torch.Tensor, Wq: torch.Ten
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(out, "Y", torch.float16, (M, N))
-    _check(lib().rrs_w4a4_gemm_per_channel(xq, ap, wq, wp, M, N, K, flags, yp,
-                                           _stream(Xq.device)), "rrs_w4a4_gemm_per_channel")
+    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    _check(lib().rrs_w4a4_gemm_scratch(xq, ap, None, wq, wp, None, M, N, K, 0, flags, yp, sp, sb,
+                                       _stream(Xq.device)), "rrs_w4a4_gemm_per_channel")
     return out
 
 
@@ -408,7 +430,8 @@ def w4a4_gemm_reorder(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Te
             _dev(block_order, "block_order", torch.int32, (K // REORDER_BLOCK,)))
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    _check(lib().rrs_w4a4_gemm_reorder(*args, M, N, K, g, flags, yp, _stream(Xq.device)),
+    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    _check(lib().rrs_w4a4_gemm_scratch(*args, M, N, K, g, flags, yp, sp, sb, _stream(Xq.device)),
            "rrs_w4a4_gemm_reorder")
     return Y
 
@@ -427,7 +450,9 @@ def linear_reorder(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: 
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    _check(lib().rrs_linear_reorder(xp, wqp, wsp, M, N, K, g, flags, yp, workspace.data_ptr(),
-                                    workspace.numel() * workspace.element_size(),
-                                    _stream(X.device)), "rrs_linear_reorder")
+    keep, sp, sb = _gemm_scratch(M, N, K, X.device)
+    _check(lib().rrs_linear_reorder_scratch(xp, wqp, wsp, M, N, K, g, flags, yp,
+                                            workspace.data_ptr(),
+                                            workspace.numel() * workspace.element_size(), sp, sb,
+                                            _stream(X.device)), "rrs_linear_reorder")
     return Y

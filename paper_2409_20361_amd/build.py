@@ -20,12 +20,15 @@ OBJDIR = os.path.join(PKG, "_build")
 
 SOURCES = ["rrs_api.cpp", "rrs_quant.hip", "rrs_weight.hip", "rrs_gemm.hip", "rrs_gemm_small.hip",
            "rrs_gemm_decode.hip", "rrs_quant_wave.hip", "rrs_reorder.hip", "rrs_quant_rows.hip",
-           "rrs_gemm_stream.hip", "rrs_gemm_stream_gather.hip", "rrs_gemm_mid.hip", "rrs_noalloc.hip"]
+           "rrs_gemm_stream.hip", "rrs_gemm_stream_gather.hip", "rrs_gemm_mid.hip",
+           "rrs_gemm_fp6.hip", "rrs_noalloc.hip"]
 
 # Per-source code-generation options on top of COMMON.
 # rrs_gemm_stream_gather.hip: keep MFMA results in VGPRs (the per-block
 #   rescale reads every accumulator; in AGPRs each read is an extra copy).
-EXTRA = {"rrs_gemm_stream_gather.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# rrs_gemm_fp6.hip: the same (every partial is read by the rescale).
+EXTRA = {"rrs_gemm_stream_gather.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "rrs_gemm_fp6.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 # -packed-fp32-ops: no v_pk_{add,mul,fma}_f32 in any kernel.
 # -ffp-contract=off: every rounding in the rotation and scale chain is an

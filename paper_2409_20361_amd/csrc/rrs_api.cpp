@@ -183,6 +183,12 @@ rrs_status check_device() {
 
 rrs_status from_hip(hipError_t e) { return e == hipSuccess ? RRS_OK : RRS_ERR_HIP; }
 
+// The GEMM of a call: on the caller's scratch where that helps and is large
+// enough, else without. s == nullptr: per-channel; border: runtime reorder.
+hipError_t run_gemm(const void* Xq, const float* a, const float* s, const void* Wq,
+                    const float* w, const int32_t* border, int M, int N, int K, int g, int flags,
+                    void* Y, void* scratch, size_t scratch_bytes, void* stream);
+
 size_t linear_ws_bytes(int M, int K, int g) {
   return rrs::quant_workspace_bytes(M, K) + rrs::align256((size_t)M * (K / 2)) +
          rrs::align256((size_t)M * 4) + rrs::align256((size_t)(K / g) * 4);
@@ -198,7 +204,7 @@ size_t linear_reorder_ws_bytes(int M, int K, int g) {
 
 rrs_status linear_run(const void* X, const void* Wq, const float* w_scale, int M, int N, int K,
                       int group_size, const int32_t* perm, int flags, void* Y, void* workspace,
-                      void* stream);
+                      void* scratch, size_t scratch_bytes, void* stream);
 
 }  // namespace
 
@@ -305,33 +311,41 @@ rrs_status rrs_rotate_smooth_quant(const void* X, int M, int K, int group_size,
                                     workspace, workspace_bytes, stream);
 }
 
-rrs_status rrs_w4a4_gemm_ex(const void* Xq, const float* a_scale, const float* s_group,
-                            const void* Wq, const float* w_scale, int M, int N, int K,
-                            int group_size, int flags, void* Y, void* stream) {
+rrs_status rrs_w4a4_gemm_scratch(const void* Xq, const float* a_scale, const float* s_group,
+                                 const void* Wq, const float* w_scale,
+                                 const int32_t* block_order, int M, int N, int K,
+                                 int group_size, int flags, void* Y, void* scratch,
+                                 size_t scratch_bytes, void* stream) {
   if (debug_enabled())
     std::fprintf(stderr,
-                 "[rrs] w4a4_gemm Xq=%p a=%p s=%p Wq=%p w=%p M=%d N=%d K=%d g=%d flags=%d "
-                 "Y=%p\n",
-                 Xq, (const void*)a_scale, (const void*)s_group, Wq, (const void*)w_scale, M, N,
-                 K, group_size, flags, Y);
-  if (!Xq || !a_scale || !s_group || !Wq || !w_scale || !Y) return RRS_ERR_NULL;
+                 "[rrs] w4a4_gemm Xq=%p a=%p s=%p Wq=%p w=%p order=%p M=%d N=%d K=%d g=%d "
+                 "flags=%d Y=%p scratch=%p (%zu B)\n",
+                 Xq, (const void*)a_scale, (const void*)s_group, Wq, (const void*)w_scale,
+                 (const void*)block_order, M, N, K, group_size, flags, Y, scratch, scratch_bytes);
+  const bool per_channel = !s_group;
+  if (!Xq || !a_scale || !Wq || !w_scale || !Y || (per_channel && block_order))
+    return RRS_ERR_NULL;
   if (!valid_m(M) || !valid_n(N) || !valid_k(K)) return RRS_ERR_SHAPE;
-  if (!valid_group(K, group_size)) return RRS_ERR_GROUP;
-  if (!valid_flags(flags, kAllFlags)) return RRS_ERR_FLAGS;
-  if (!is_aligned(Xq) || !is_aligned(a_scale) || !is_aligned(s_group) || !is_aligned(Wq) ||
-      !is_aligned(w_scale) || !is_aligned(Y))
+  if (!per_channel && !valid_group(K, group_size)) return RRS_ERR_GROUP;
+  if (!valid_flags(flags, block_order ? kRotationFlags : kAllFlags)) return RRS_ERR_FLAGS;
+  if (!is_aligned(Xq) || !is_aligned(a_scale) || (s_group && !is_aligned(s_group)) ||
+      !is_aligned(Wq) || !is_aligned(w_scale) || !is_aligned(Y) ||
+      (block_order && !is_aligned(block_order)) || (scratch && !is_aligned(scratch)))
     return RRS_ERR_ALIGN;
   if (rrs_status s = check_device()) return s;
-  if (debug_enabled()) {
+  if (debug_enabled() && !per_channel) {  // as the plain entry points
+    if (block_order)
+      if (rrs_status s =
+              debug_check_perm(block_order, K / RRS_REORDER_BLOCK, "block_order", stream))
+        return s;
     if (rrs_status s = debug_check_finite_f32(a_scale, (size_t)M, "a_scale", stream)) return s;
-    if (rrs_status s = debug_check_finite_f32(s_group, (size_t)(K / group_size), "s_group", stream))
+    if (rrs_status s =
+            debug_check_finite_f32(s_group, (size_t)(K / group_size), "s_group", stream))
       return s;
     if (rrs_status s = debug_check_finite_f32(w_scale, (size_t)N, "w_scale", stream)) return s;
   }
-  return from_hip(rrs::launch_w4a4_gemm(
-      static_cast<const uint8_t*>(Xq), a_scale, s_group, static_cast<const uint8_t*>(Wq),
-      w_scale, M, N, K, group_size, static_cast<uint16_t*>(Y), out_scale(K, flags),
-      static_cast<hipStream_t>(stream), layout(flags)));
+  return from_hip(run_gemm(Xq, a_scale, s_group, Wq, w_scale, block_order, M, N, K, group_size,
+                           flags, Y, scratch, scratch_bytes, stream));
 }
 
 rrs_status rrs_w4a4_gemm(const void* Xq, const float* a_scale, const float* s_group,
@@ -340,9 +354,10 @@ rrs_status rrs_w4a4_gemm(const void* Xq, const float* a_scale, const float* s_gr
   return rrs_w4a4_gemm_ex(Xq, a_scale, s_group, Wq, w_scale, M, N, K, group_size, 0, Y, stream);
 }
 
-rrs_status rrs_linear_ex(const void* X, const void* Wq, const float* w_scale, int M, int N,
-                         int K, int group_size, const int32_t* perm, int flags, void* Y,
-                         void* workspace, size_t workspace_bytes, void* stream) {
+rrs_status rrs_linear_scratch(const void* X, const void* Wq, const float* w_scale, int M, int N,
+                              int K, int group_size, const int32_t* perm, int flags, void* Y,
+                              void* workspace, size_t workspace_bytes, void* scratch,
+                              size_t scratch_bytes, void* stream) {
   if (debug_enabled())
     std::fprintf(stderr,
                  "[rrs] linear X=%p Wq=%p w=%p M=%d N=%d K=%d g=%d perm=%p flags=%d Y=%p ws=%p "
@@ -354,7 +369,7 @@ rrs_status rrs_linear_ex(const void* X, const void* Wq, const float* w_scale, in
   if (!valid_group(K, group_size)) return RRS_ERR_GROUP;
   if (!valid_flags(flags, kAllFlags)) return RRS_ERR_FLAGS;
   if (!is_aligned(X) || !is_aligned(Wq) || !is_aligned(w_scale) || !is_aligned(Y) ||
-      !is_aligned(workspace) || (perm && !is_aligned(perm)))
+      !is_aligned(workspace) || (perm && !is_aligned(perm)) || (scratch && !is_aligned(scratch)))
     return RRS_ERR_ALIGN;
   if (workspace_bytes < linear_ws_bytes(M, K, group_size)) return RRS_ERR_WORKSPACE;
   if (rrs_status s = check_device()) return s;
@@ -363,7 +378,8 @@ rrs_status rrs_linear_ex(const void* X, const void* Wq, const float* w_scale, in
     if (rrs_status s = debug_check_perm(perm, K, "perm", stream)) return s;
     if (rrs_status s = debug_check_finite_f32(w_scale, (size_t)N, "w_scale", stream)) return s;
   }
-  return linear_run(X, Wq, w_scale, M, N, K, group_size, perm, flags, Y, workspace, stream);
+  return linear_run(X, Wq, w_scale, M, N, K, group_size, perm, flags, Y, workspace, scratch,
+                    scratch_bytes, stream);
 }
 
 }  // extern "C"
@@ -374,7 +390,7 @@ namespace {
 // the workspace (rrs_linear_workspace_bytes bytes).
 rrs_status linear_run(const void* X, const void* Wq, const float* w_scale, int M, int N, int K,
                       int group_size, const int32_t* perm, int flags, void* Y, void* workspace,
-                      void* stream) {
+                      void* scratch, size_t scratch_bytes, void* stream) {
   char* ws = static_cast<char*>(workspace);
   void* qws = ws;
   ws += rrs::quant_workspace_bytes(M, K);
@@ -395,17 +411,57 @@ rrs_status linear_run(const void* X, const void* Wq, const float* w_scale, int M
                                                  group_size, perm, flags & kQuantFlags, xq, a,
                                                  s, qws, st);
   if (e != hipSuccess) return RRS_ERR_HIP;
-  const rrs_status r = from_hip(rrs::launch_w4a4_gemm(
-      xq, a, s, static_cast<const uint8_t*>(Wq), w_scale, M, N, K, group_size,
-      static_cast<uint16_t*>(Y), out_scale(K, flags), st, layout(flags)));
+  const rrs_status r = from_hip(run_gemm(xq, a, s, Wq, w_scale, nullptr, M, N, K, group_size,
+                                         flags, Y, scratch, scratch_bytes, stream));
   if (r == RRS_OK && debug_enabled())
     return debug_check_quant_wait(M, K, group_size, perm, flags, qws, stream);
   return r;
 }
 
+hipError_t run_gemm(const void* Xq, const float* a, const float* s, const void* Wq,
+                    const float* w, const int32_t* border, int M, int N, int K, int g, int flags,
+                    void* Y, void* scratch, size_t scratch_bytes, void* stream) {
+  const uint8_t* xq = static_cast<const uint8_t*>(Xq);
+  const uint8_t* wq = static_cast<const uint8_t*>(Wq);
+  uint16_t* y = static_cast<uint16_t*>(Y);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const float os = out_scale(K, flags);
+  const rrs::WqLayout lay = layout(flags);
+  if (scratch) {
+    const size_t need = rrs::fp6_scratch_bytes(M, N, K);
+    if (need && scratch_bytes >= need)
+      return rrs::launch_w4a4_gemm_fp6(xq, a, s, wq, w, border, M, N, K, g, y, os, scratch, st,
+                                       lay);
+  }
+  if (!s) return rrs::launch_w4a4_gemm_per_channel(xq, a, wq, w, M, N, K, y, os, st, lay);
+  if (border)
+    return rrs::launch_w4a4_gemm_reorder(xq, a, s, wq, w, border, M, N, K, g, y, os, st, lay);
+  return rrs::launch_w4a4_gemm(xq, a, s, wq, w, M, N, K, g, y, os, st, lay);
+}
+
 }  // namespace
 
 extern "C" {
+
+size_t rrs_gemm_scratch_bytes(int M, int N, int K) {
+  if (!valid_m(M) || !valid_n(N) || !valid_k(K)) return 0;
+  return rrs::fp6_scratch_bytes(M, N, K);
+}
+
+rrs_status rrs_w4a4_gemm_ex(const void* Xq, const float* a_scale, const float* s_group,
+                            const void* Wq, const float* w_scale, int M, int N, int K,
+                            int group_size, int flags, void* Y, void* stream) {
+  if (!s_group) return RRS_ERR_NULL;
+  return rrs_w4a4_gemm_scratch(Xq, a_scale, s_group, Wq, w_scale, nullptr, M, N, K, group_size,
+                               flags, Y, nullptr, 0, stream);
+}
+
+rrs_status rrs_linear_ex(const void* X, const void* Wq, const float* w_scale, int M, int N,
+                         int K, int group_size, const int32_t* perm, int flags, void* Y,
+                         void* workspace, size_t workspace_bytes, void* stream) {
+  return rrs_linear_scratch(X, Wq, w_scale, M, N, K, group_size, perm, flags, Y, workspace,
+                            workspace_bytes, nullptr, 0, stream);
+}
 
 rrs_status rrs_linear(const void* X, const void* Wq, const float* w_scale, int M, int N,
                       int K, int group_size, const int32_t* perm, void* Y, void* workspace,
@@ -440,7 +496,7 @@ rrs_status rrs_linear_noalloc(const void* X, const void* Wq, const float* w_scal
     (void)hipGetLastError();
     return RRS_ERR_HIP;
   }
-  return linear_run(X, Wq, w_scale, M, N, K, group_size, perm, 0, Y, ws, stream);
+  return linear_run(X, Wq, w_scale, M, N, K, group_size, perm, 0, Y, ws, nullptr, 0, stream);
 }
 
 rrs_status rrs_quantize_sub_channel(const void* X, int M, int K, int group_size, int flags,
@@ -570,34 +626,22 @@ rrs_status rrs_w4a4_gemm_reorder(const void* Xq, const float* a_scale, const flo
                                  const void* Wq, const float* w_scale,
                                  const int32_t* block_order, int M, int N, int K,
                                  int group_size, int flags, void* Y, void* stream) {
-  if (debug_enabled())
-    std::fprintf(stderr, "[rrs] w4a4_gemm_reorder M=%d N=%d K=%d g=%d flags=%d order=%p\n", M,
-                 N, K, group_size, flags, (const void*)block_order);
-  if (!Xq || !a_scale || !s_group || !Wq || !w_scale || !block_order || !Y) return RRS_ERR_NULL;
-  if (!valid_m(M) || !valid_n(N) || !valid_k(K)) return RRS_ERR_SHAPE;
-  if (!valid_group(K, group_size)) return RRS_ERR_GROUP;
-  if (!valid_flags(flags, kRotationFlags)) return RRS_ERR_FLAGS;
-  if (!is_aligned(Xq) || !is_aligned(a_scale) || !is_aligned(s_group) || !is_aligned(Wq) ||
-      !is_aligned(w_scale) || !is_aligned(block_order) || !is_aligned(Y))
-    return RRS_ERR_ALIGN;
-  if (rrs_status s = check_device()) return s;
-  if (debug_enabled()) {
-    if (rrs_status s = debug_check_perm(block_order, K / RRS_REORDER_BLOCK, "block_order", stream))
-      return s;
-    if (rrs_status s = debug_check_finite_f32(a_scale, (size_t)M, "a_scale", stream)) return s;
-    if (rrs_status s = debug_check_finite_f32(s_group, (size_t)(K / group_size), "s_group", stream))
-      return s;
-    if (rrs_status s = debug_check_finite_f32(w_scale, (size_t)N, "w_scale", stream)) return s;
-  }
-  return from_hip(rrs::launch_w4a4_gemm_reorder(
-      static_cast<const uint8_t*>(Xq), a_scale, s_group, static_cast<const uint8_t*>(Wq),
-      w_scale, block_order, M, N, K, group_size, static_cast<uint16_t*>(Y), out_scale(K, flags),
-      static_cast<hipStream_t>(stream), layout(flags)));
+  if (!s_group || !block_order) return RRS_ERR_NULL;
+  return rrs_w4a4_gemm_scratch(Xq, a_scale, s_group, Wq, w_scale, block_order, M, N, K, group_size,
+                               flags, Y, nullptr, 0, stream);
 }
 
 rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scale, int M,
                               int N, int K, int group_size, int flags, void* Y, void* workspace,
                               size_t workspace_bytes, void* stream) {
+  return rrs_linear_reorder_scratch(X, Wq, w_scale, M, N, K, group_size, flags, Y, workspace,
+                                    workspace_bytes, nullptr, 0, stream);
+}
+
+rrs_status rrs_linear_reorder_scratch(const void* X, const void* Wq, const float* w_scale, int M,
+                                      int N, int K, int group_size, int flags, void* Y,
+                                      void* workspace, size_t workspace_bytes, void* scratch,
+                                      size_t scratch_bytes, void* stream) {
   if (debug_enabled())
     std::fprintf(stderr,
                  "[rrs] linear_reorder X=%p Wq=%p w=%p M=%d N=%d K=%d g=%d flags=%d Y=%p ws=%p "
@@ -609,7 +653,7 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
   if (!valid_group(K, group_size)) return RRS_ERR_GROUP;
   if (!valid_flags(flags, kRotationFlags)) return RRS_ERR_FLAGS;
   if (!is_aligned(X) || !is_aligned(Wq) || !is_aligned(w_scale) || !is_aligned(Y) ||
-      !is_aligned(workspace))
+      !is_aligned(workspace) || (scratch && !is_aligned(scratch)))
     return RRS_ERR_ALIGN;
   if (workspace_bytes < linear_reorder_ws_bytes(M, K, group_size)) return RRS_ERR_WORKSPACE;
   if (rrs_status s = check_device()) return s;
@@ -634,9 +678,8 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
       static_cast<const uint16_t*>(X), M, K, group_size, flags & RRS_SKIP_ROTATION, xq, a, s,
       order, qws, st);
   if (e != hipSuccess) return RRS_ERR_HIP;
-  const rrs_status r = from_hip(rrs::launch_w4a4_gemm_reorder(
-      xq, a, s, static_cast<const uint8_t*>(Wq), w_scale, order, M, N, K, group_size,
-      static_cast<uint16_t*>(Y), out_scale(K, flags), st, layout(flags)));
+  const rrs_status r = from_hip(run_gemm(xq, a, s, Wq, w_scale, order, M, N, K, group_size, flags,
+                                         Y, scratch, scratch_bytes, stream));
   if (r == RRS_OK && debug_enabled()) return debug_check_reorder_wait(M, K, qws, stream);
   return r;
 }

@@ -155,6 +155,16 @@ hipError_t launch_w4a4_gemm_mid_per_channel(const uint8_t* Xq, const float* a_sc
 hipError_t launch_w4a4_gemm_mid_partials(const uint8_t* Xq, const uint8_t* Wq, int M, int N, int K,
                                          int g, int32_t* P, hipStream_t stream);
 
+// Many tokens on the 6-bit matrix rate (rrs_gemm_fp6.hip), with scratch memory of
+// the caller for the spread token codes: the main kernel's results bit for bit.
+// fp6_scratch_bytes is 0 where another kernel serves. s_group == nullptr:
+// per-channel (border must be nullptr too).
+size_t fp6_scratch_bytes(int M, int N, int K);
+hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                                const uint8_t* Wq, const float* w_scale, const int32_t* border,
+                                int M, int N, int K, int g, uint16_t* Y, float out_scale,
+                                void* scratch, hipStream_t stream, WqLayout lay);
+
 // Weight-streaming kernel for few tokens (rrs_gemm_stream.hip): each
 // workgroup copies 16 whole rows of Wq into LDS with direct-to-LDS loads.
 // Up to 16 tokens, K >= 4 g (not K = 16384 with g <= 128). Both layouts,

@@ -1,0 +1,98 @@
+"""The many-token GEMM on scratch memory (6-bit operands) against the entry points
+without scratch (int8 operands): the partials of both are exact and each is
+added with one FMA in the same order, so Y must be the same bits. Codes are all
+sixteen nibbles, at the edges of the tiles: ragged rows (a last block of 32 rows
+partly or wholly past M) and columns, both tile shapes, every group size (64 at K =
+16384: more groups than one register of scales), both weight layouts, the
+runtime reorder's table and the per-channel scheme. -0 and rounding cannot hide
+anything: the comparison is on the bits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_20361_amd as rrs
+    rrs.lib()
+
+
+def _st():
+    return torch.cuda.current_stream().cuda_stream
+
+
+CASES = [  # 128 x 128 tiles, then 256 x 128
+    (500, 512, 6208, 128, False), (777, 1024, 4160, 64, True), (770, 16384, 4112, 64, False),
+    (513, 2048, 6176, 512, True),
+    (1030, 1024, 5200, 128, True), (1057, 512, 5136, 64, False), (1300, 2048, 6160, 256, False),
+    (2049, 1024, 4624, 512, False),
+]
+
+
+@pytest.mark.parametrize("M,K,N,g,tiled", CASES)
+def test_scratch_gemm_same_bits(M, K, N, g, tiled):
+    import paper_2409_20361_amd as rrs
+    lib = rrs.lib()
+    print(f"[case] scratch GEMM M={M} K={K} N={N} g={g} tiled={tiled}", flush=True)
+    need = lib.rrs_gemm_scratch_bytes(M, N, K)
+    assert need > 0
+    gen = torch.Generator(device="cuda").manual_seed(M + K + N)
+    Xq = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device="cuda", generator=gen)
+    Wq = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device="cuda", generator=gen)
+    Xq[M // 2] = 0x88                                   # a row of -8 ...
+    Wq[:16] = 0x88                                      # ... against columns of -8
+    a = torch.rand(M, device="cuda", generator=gen) * 1e-2
+    s = torch.exp(6 * torch.rand(K // g, device="cuda", generator=gen) - 3)
+    w = torch.rand(N, device="cuda", generator=gen) * 1e-2
+    order = torch.randperm(K // 32, device="cuda", generator=gen).to(torch.int32)
+    fl = rrs.WEIGHT_TILED if tiled else 0
+    p = [t.data_ptr() for t in (Xq, a, s, Wq, w)]
+    for form in ("plain", "reorder", "per_channel"):
+        Y = [torch.full((M, N), 7.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+        y = Y[0].data_ptr()
+        if form == "plain":
+            code = lib.rrs_w4a4_gemm_ex(*p, M, N, K, g, fl, y, _st())
+            rrs.w4a4_gemm(Xq, a, s, Wq, w, g, out=Y[1], flags=fl)
+        elif form == "reorder":
+            code = lib.rrs_w4a4_gemm_reorder(*p, order.data_ptr(), M, N, K, g, fl, y, _st())
+            rrs.w4a4_gemm_reorder(Xq, a, s, Wq, w, order, g, out=Y[1], flags=fl)
+        else:
+            code = lib.rrs_w4a4_gemm_per_channel(p[0], p[1], p[3], p[4], M, N, K, fl, y, _st())
+            rrs.w4a4_gemm_per_channel(Xq, a, Wq, w, out=Y[1], flags=fl)
+        assert code == 0
+        torch.cuda.synchronize()
+        bits = [t.view(torch.int16) for t in Y]
+        assert torch.equal(*bits), f"{form}: {int((bits[0] != bits[1]).sum())} outputs differ"
+
+
+def test_scratch_buffer_is_optional():
+    import paper_2409_20361_amd as rrs
+    lib = rrs.lib()
+    M, K, N, g = 500, 512, 6208, 128
+    need = lib.rrs_gemm_scratch_bytes(M, N, K)
+    X = torch.randn(M, K, device="cuda").half()
+    Wq, w = rrs.prepare_weight((0.02 * torch.randn(K, N, device="cuda")).half())
+    ws = torch.zeros(rrs.linear_workspace_bytes(M, K, g), dtype=torch.uint8, device="cuda")
+    buf = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+
+    def call(scratch, nbytes):
+        Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        code = lib.rrs_linear_scratch(X.data_ptr(), Wq.data_ptr(), w.data_ptr(), M, N, K, g, None,
+                                      0, Y.data_ptr(), ws.data_ptr(), ws.numel(), scratch, nbytes,
+                                      _st())
+        torch.cuda.synchronize()
+        return code, Y
+
+    code, ref = call(None, 0)
+    assert code == 0
+    for nbytes in (need, need - 1):                     # just enough; too small: the plain path
+        code, Y = call(buf.data_ptr(), nbytes)
+        assert code == 0 and torch.equal(Y, ref)
+    assert bool((buf[need:] == 0xA5).all())             # nothing written past it
+    assert call(buf.data_ptr() + 8, need)[0] == -4      # not 16-byte aligned
+    assert lib.rrs_gemm_scratch_bytes(16, N, K) == 0    # few tokens use none
