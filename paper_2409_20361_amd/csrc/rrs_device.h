@@ -94,44 +94,49 @@ __device__ __forceinline__ int window_index(int t, int e, int lo, int L) {
   return (t & ((1 << lo) - 1)) | (e << lo) | ((t >> lo) << (lo + L));
 }
 
-template <int K>
+// RT threads per row (a power of two).
+template <int K, int RT = kRowThreads>
 struct FwhtShape {
-  static constexpr int E = K / kRowThreads;
+  static constexpr int E = K / RT;
   static constexpr int L = ilog2(E);
   static constexpr int LOGK = ilog2(K);
   static constexpr int kWindows = (LOGK + L - 1) / L;
-  static constexpr int kFinalLo = LOGK - L;  // == kLogRowThreads
-  static_assert(E >= 2 && (1 << L) == E, "K must be 2^(8+L), L >= 1");
+  static constexpr int kFinalLo = LOGK - L;  // == log2(RT)
+  static_assert(E >= 2 && (1 << L) == E, "K must be RT 2^L, L >= 1");
 };
 
-template <int K, int W, bool kRot>
-__device__ __forceinline__ void fwht_windows(float (&v)[FwhtShape<K>::E], float* lds, int t) {
-  using S = FwhtShape<K>;
+template <int K, int W, bool kRot, int RT = kRowThreads>
+__device__ __forceinline__ void fwht_windows(float (&v)[K / RT], float* lds, int t) {
+  using S = FwhtShape<K, RT>;
   if constexpr (W < S::kWindows) {
     constexpr int prev_lo = (W - 1) * S::L;
     constexpr int lo = (W * S::L < S::LOGK - S::L) ? W * S::L : S::LOGK - S::L;
     constexpr int first = W * S::L - lo;  // first e-bit not yet transformed
+    // The bits of e and of t are disjoint, so the padded address is a thread's
+    // base plus a constant per e, which the LDS instruction holds as its offset.
     __syncthreads();  // earlier readers of lds are done
+    float* wr = lds + lds_pad(window_index(t, 0, prev_lo, S::L));
 #pragma unroll
-    for (int e = 0; e < S::E; ++e) lds[lds_pad(window_index(t, e, prev_lo, S::L))] = v[e];
+    for (int e = 0; e < S::E; ++e) wr[lds_pad(e << prev_lo)] = v[e];
     __syncthreads();
+    const float* rd = lds + lds_pad(window_index(t, 0, lo, S::L));
 #pragma unroll
-    for (int e = 0; e < S::E; ++e) v[e] = lds[lds_pad(window_index(t, e, lo, S::L))];
+    for (int e = 0; e < S::E; ++e) v[e] = rd[lds_pad(e << lo)];
     if constexpr (kRot) fwht_stages<S::E, first, S::L>(v);
-    fwht_windows<K, W + 1, kRot>(v, lds, t);
+    fwht_windows<K, W + 1, kRot, RT>(v, lds, t);
   }
 }
 
 // On entry v[e] holds element t*E + e of the row. On exit v[e] holds element
-// t + e * 256 of x H_K (of x itself when kRot is false: the same data
+// t + e RT of x H_K (of x itself when kRot is false: the same data
 // movement without the butterflies, for the ablation without rotation).
 // `lds` must hold lds_row_floats(K) floats; it is clobbered. Must be called by
-// all 256 threads of the workgroup.
-template <int K, bool kRot = true>
-__device__ __forceinline__ void fwht_row(float (&v)[FwhtShape<K>::E], float* lds, int t) {
-  using S = FwhtShape<K>;
+// all threads of the workgroup.
+template <int K, bool kRot = true, int RT = kRowThreads>
+__device__ __forceinline__ void fwht_row(float (&v)[K / RT], float* lds, int t) {
+  using S = FwhtShape<K, RT>;
   if constexpr (kRot) fwht_stages<S::E, 0, S::L>(v);
-  fwht_windows<K, 1, kRot>(v, lds, t);
+  fwht_windows<K, 1, kRot, RT>(v, lds, t);
 }
 
 // LDS address of position q of the rotated row in position-major order: row

@@ -18,6 +18,8 @@
 // works on one row at a time. Cross-team and cross-wave reductions go through
 // LDS, no atomics. K = 4096 (and K = 2048 with many rows) takes the
 // one-wave-per-row kernels of rrs_quant_wave.hip instead.
+#include <type_traits>
+
 #include "rrs_device.h"
 #include "rrs_internal.h"
 
@@ -41,10 +43,10 @@ constexpr int slot_floats() {
 }
 
 // v = row r of X (this thread's E elements), or zeros past the last row r1.
-template <int K>
+template <int K, int RT = kRowThreads>
 __device__ __forceinline__ void load_row_or_zero(const uint16_t* __restrict__ X, int r, int r1,
-                                                 int t, float (&v)[FwhtShape<K>::E]) {
-  constexpr int E = FwhtShape<K>::E;
+                                                 int t, float (&v)[K / RT]) {
+  constexpr int E = FwhtShape<K, RT>::E;
   if (r < r1) {
     load_halves<E>(X + (size_t)r * K + (size_t)t * E, v);
   } else {
@@ -53,26 +55,43 @@ __device__ __forceinline__ void load_row_or_zero(const uint16_t* __restrict__ X,
   }
 }
 
-// Per-channel maxima cm (this thread's E channels t + 256 e) of every team
+// Teams of the two-pass kernels: T teams of RT threads per workgroup, one row
+// each at a time. Up to K = 4096 four teams of 256 threads, the next rows
+// requested while the current ones are transformed. From K = 8192 a thread holds 32
+// elements (RT = 256, or 512 at K = 16384) and no next row, so that four waves fit
+// on a SIMD (128 registers) and cover each other's LDS and memory waits: with 64
+// elements and the next row at K = 16384 (354 to 401 registers, one wave per SIMD) a
+// row took about 9 us a pass. One, two or four teams by the rows a workgroup has.
+template <int K, int T>
+struct RowTeams {
+  static constexpr int RT = K == 16384 ? 512 : kRowThreads;
+  static constexpr int threads = T * RT;
+  static constexpr bool kAhead = K <= 4096;
+  static constexpr int slot_floats =
+      T * lds_row_floats(K) > 1024 ? T * lds_row_floats(K) : 1024;
+};
+
+// Per-channel maxima cm (this thread's E channels t + RT e) of every team
 // combined into cbuf[0, K). Must be called by all threads of the workgroup;
 // cbuf holds >= K floats.
-template <int K, int kTeams = Teams<K>::n>
-__device__ __forceinline__ void combine_teams(const float (&cm)[FwhtShape<K>::E], float* cbuf) {
-  constexpr int E = FwhtShape<K>::E;
+template <int K, int kTeams, int RT = kRowThreads>
+__device__ __forceinline__ void combine_teams(const float (&cm)[K / RT],
+                                              float* cbuf) {
+  constexpr int E = FwhtShape<K, RT>::E;
   const int tid = threadIdx.x;
-  const int team = tid >> 8;
-  const int t = tid & (kRowThreads - 1);
+  const int team = tid / RT;
+  const int t = tid & (RT - 1);
   __syncthreads();
   if (team == 0) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) cbuf[t + e * kRowThreads] = cm[e];
+    for (int e = 0; e < E; ++e) cbuf[t + e * RT] = cm[e];
   }
   __syncthreads();
   for (int tm = 1; tm < kTeams; ++tm) {
     if (team == tm) {
 #pragma unroll
       for (int e = 0; e < E; ++e)
-        cbuf[t + e * kRowThreads] = fmaxf(cbuf[t + e * kRowThreads], cm[e]);
+        cbuf[t + e * RT] = fmaxf(cbuf[t + e * RT], cm[e]);
     }
     __syncthreads();
   }
@@ -82,12 +101,12 @@ __device__ __forceinline__ void combine_teams(const float (&cm)[FwhtShape<K>::E]
 // each group of g (reordered) positions. Returns, for threads tid < K / g, the
 // maximum of group tid; 0 elsewhere. Must be called by all threads of the
 // workgroup; cbuf holds >= K floats.
-template <int K, int kTeams = Teams<K>::n>
-__device__ __forceinline__ float group_maxima(const float (&cm)[FwhtShape<K>::E], float* cbuf,
+template <int K, int kTeams, int RT = kRowThreads>
+__device__ __forceinline__ float group_maxima(const float (&cm)[K / RT], float* cbuf,
                                               int g, const int32_t* __restrict__ perm) {
-  constexpr int kThreads = kTeams * kRowThreads;
+  constexpr int kThreads = kTeams * RT;
   const int tid = threadIdx.x;
-  combine_teams<K, kTeams>(cm, cbuf);
+  combine_teams<K, kTeams, RT>(cm, cbuf);
   // The first NA threads cover P consecutive positions each, all inside one
   // group (P <= 64 <= g).
   constexpr int NA = K < kThreads ? K : kThreads;
@@ -119,19 +138,19 @@ __device__ __forceinline__ float group_maxima(const float (&cm)[FwhtShape<K>::E]
 // kBlocks (runtime reorder): the row written holds instead the maxima of the
 // K / 32 blocks of 32 consecutive channels, in natural order (g and perm are
 // not used).
-template <int K, bool kRot, bool kBlocks = false>
-__global__ __launch_bounds__(Teams<K>::threads) void rot_max_kernel(
+template <int K, bool kRot, bool kBlocks, int kTeams>
+__global__ __launch_bounds__((RowTeams<K, kTeams>::threads)) void rot_max_kernel(
     const uint16_t* __restrict__ X, int M, int g, int rows_per_wg,
     const int32_t* __restrict__ perm, float* __restrict__ gpart) {
-  using S = FwhtShape<K>;
-  constexpr int E = S::E;
+  using RTm = RowTeams<K, kTeams>;
+  constexpr int RT = RTm::RT;
+  constexpr int E = FwhtShape<K, RT>::E;
   constexpr int RF = lds_row_floats(K);
-  constexpr int kTeams = Teams<K>::n;
-  __shared__ float slots[slot_floats<K>()];
+  __shared__ float slots[RTm::slot_floats];
   float* cbuf = slots;  // reduction scratch once the rows are done
   const int tid = threadIdx.x;
-  const int team = tid >> 8;
-  const int t = tid & (kRowThreads - 1);
+  const int team = tid / RT;
+  const int t = tid & (RT - 1);
   const int iters = (rows_per_wg + kTeams - 1) / kTeams;
   const int r0 = blockIdx.x * rows_per_wg;
   const int r1 = min(M, r0 + rows_per_wg);
@@ -140,28 +159,32 @@ __global__ __launch_bounds__(Teams<K>::threads) void rot_max_kernel(
   float cm[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) cm[e] = 0.0f;
-  float vn[E];  // next row, loaded while the current one is transformed
-  load_row_or_zero<K>(X, r0 + team, r1, t, vn);
+  float vn[RTm::kAhead ? E : 1];  // next row, loaded while the current one is transformed
+  if constexpr (RTm::kAhead) load_row_or_zero<K, RT>(X, r0 + team, r1, t, vn);
   for (int it = 0; it < iters; ++it) {
     float v[E];
+    if constexpr (RTm::kAhead) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = vn[e];
-    if (it + 1 < iters) load_row_or_zero<K>(X, r0 + (it + 1) * kTeams + team, r1, t, vn);
-    fwht_row<K, kRot>(v, slot, t);  // v[e] = y[t + 256 e]
+      for (int e = 0; e < E; ++e) v[e] = vn[e];
+      if (it + 1 < iters) load_row_or_zero<K, RT>(X, r0 + (it + 1) * kTeams + team, r1, t, vn);
+    } else {
+      load_row_or_zero<K, RT>(X, r0 + it * kTeams + team, r1, t, v);
+    }
+    fwht_row<K, kRot, RT>(v, slot, t);  // v[e] = y[t + RT e]
 #pragma unroll
     for (int e = 0; e < E; ++e) cm[e] = fmaxf(cm[e], fabsf(v[e]));
   }
   if constexpr (kBlocks) {
-    combine_teams<K>(cm, cbuf);
+    combine_teams<K, kTeams, RT>(cm, cbuf);
     float* out = gpart + (size_t)blockIdx.x * (K / 32);
-    for (int B = tid; B < K / 32; B += Teams<K>::threads) {
+    for (int B = tid; B < K / 32; B += RTm::threads) {
       float m = 0.0f;
       // start at a different channel per thread: fewer LDS bank conflicts
       for (int q = 0; q < 32; ++q) m = fmaxf(m, cbuf[B * 32 + ((q + B) & 31)]);
       out[B] = m;
     }
   } else {
-    const float s = group_maxima<K>(cm, cbuf, g, perm);
+    const float s = group_maxima<K, kTeams, RT>(cm, cbuf, g, perm);
     if (tid < K / g) gpart[(size_t)blockIdx.x * (K / g) + tid] = s;
   }
 }
@@ -173,19 +196,20 @@ __global__ __launch_bounds__(Teams<K>::threads) void rot_max_kernel(
 // workgroup ranks the blocks itself (block_order_wg), takes s_b over the
 // sorted blocks of group b and reads position j from channel
 // 32 sblk[j / 32] + j % 32; workgroup 0 writes s_group and block_order.
-template <int K, bool kRot, bool kSmooth, bool kOrder = false>
-__global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
+template <int K, bool kRot, bool kSmooth, bool kOrder, int kTeams>
+__global__ __launch_bounds__((RowTeams<K, kTeams>::threads)) void quant_kernel(
     const uint16_t* __restrict__ X, int M, int g, int rows_per_wg, int nparts,
     const int32_t* __restrict__ perm, const float* __restrict__ gpart,
     uint8_t* __restrict__ Xq, float* __restrict__ a_scale, float* __restrict__ s_group,
     int32_t* __restrict__ block_order = nullptr) {
-  using S = FwhtShape<K>;
-  constexpr int E = S::E;
+  using RTm = RowTeams<K, kTeams>;
+  constexpr int RT = RTm::RT;
+  constexpr int WT = RT / 64;  // waves per team
+  constexpr int E = FwhtShape<K, RT>::E;
   constexpr int RF = lds_row_floats(K);
-  constexpr int kTeams = Teams<K>::n;
-  constexpr int kThreads = Teams<K>::threads;
+  constexpr int kThreads = RTm::threads;
   constexpr int NB = K / kReorderBlock;
-  __shared__ __attribute__((aligned(16))) float slots[slot_floats<K>()];
+  __shared__ __attribute__((aligned(16))) float slots[RTm::slot_floats];
   __shared__ float rg[256];
   __shared__ float red[16];
   __shared__ __attribute__((aligned(16))) unsigned long long key[kOrder ? NB : 2];
@@ -195,8 +219,8 @@ __global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
   __shared__ __attribute__((aligned(16))) float ored[kOrder ? 4 * kThreads : 4];
   float* cbuf = slots;  // reduction scratch before the rows start
   const int tid = threadIdx.x;
-  const int team = tid >> 8;
-  const int t = tid & (kRowThreads - 1);
+  const int team = tid / RT;
+  const int t = tid & (RT - 1);
   const int G = K / g;
   float* slot = slots + team * RF;
 
@@ -205,8 +229,8 @@ __global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
   const int iters = (rows_per_wg + kTeams - 1) / kTeams;
   const int r0 = blockIdx.x * rows_per_wg;
   const int r1 = min(M, r0 + rows_per_wg);
-  float vn[E];  // next row, loaded while the current one is processed
-  load_row_or_zero<K>(X, r0 + team, r1, t, vn);
+  float vn[E];  // the first row; up to K = 4096 always the next one
+  load_row_or_zero<K, RT>(X, r0 + team, r1, t, vn);
 
   if constexpr (!kSmooth) {
     // Ablation without smoothing: every scale is 1 (rotation + per-token only).
@@ -255,15 +279,29 @@ __global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
     }
     __syncthreads();
   }
-  int src[E];  // position t*E + e of the reordered row reads channel src[e]
+  // With a reorder, position t E + e of the row reads channel src(e). Four at a time
+  // from perm (16-byte aligned; L1 and L2 hold it), so that they take no registers
+  // over the rows; with the runtime reorder all E lie in one block (E <= 32).
+  auto src4 = [&](int e, int (&c)[4]) {
+    if constexpr (kOrder) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = t * E + e;
-    if constexpr (kOrder)  // masked into range, whatever the partial rows held
-      src[e] = (sblk[j / kReorderBlock] & (NB - 1)) * kReorderBlock + j % kReorderBlock;
-    else
-      src[e] = perm ? perm[j] : j;
-  }
+      for (int i = 0; i < 4; ++i) {  // masked into range, whatever the partial rows held
+        const int j = t * E + e + i;
+        c[i] = (sblk[j / kReorderBlock] & (NB - 1)) * kReorderBlock + j % kReorderBlock;
+      }
+    } else {
+      if constexpr (E >= 4) {
+        const int4 x = *reinterpret_cast<const int4*>(perm + t * E + e);
+        c[0] = x.x;
+        c[1] = x.y;
+        c[2] = x.z;
+        c[3] = x.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < E; ++i) c[i] = perm[t * E + i];
+      }
+    }
+  };
   const float rb = rg[(t * E) / g];  // this thread's positions lie in one group
 
   for (int it = 0; it < iters; ++it) {
@@ -272,23 +310,35 @@ __global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
     float v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = vn[e];
-    if (it + 1 < iters) load_row_or_zero<K>(X, r0 + (it + 1) * kTeams + team, r1, t, vn);
-    fwht_row<K, kRot>(v, slot, t);
+    if constexpr (RTm::kAhead)
+      if (it + 1 < iters) load_row_or_zero<K, RT>(X, r0 + (it + 1) * kTeams + team, r1, t, vn);
+    fwht_row<K, kRot, RT>(v, slot, t);
     // back to natural order through LDS, with the static reorder applied
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < E; ++e) slot[lds_pad(t + e * kRowThreads)] = v[e];
+    for (int e = 0; e < E; ++e) slot[lds_pad(t) + lds_pad(e * RT)] = v[e];  // disjoint bits
     __syncthreads();
+    if (!kOrder && !perm) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = slot[lds_pad(src[e])];
+      for (int e = 0; e < E; ++e) v[e] = slot[lds_pad(t * E) + lds_pad(e)];
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        int c[4];
+        src4(e, c);
+#pragma unroll
+        for (int i = 0; i < 4 && e + i < E; ++i) v[e + i] = slot[lds_pad(c[i])];
+      }
+    }
     float lm = 0.0f;
 #pragma unroll
     for (int e = 0; e < E; ++e) lm = fmaxf(lm, fabsf(v[e]));
     lm = wave_max(lm * rb);  // fl(M_ib * r_b), max over the wave
     if ((tid & 63) == 0) red[tid >> 6] = lm;
     __syncthreads();
-    const float a = fmaxf(fmaxf(red[team * 4], red[team * 4 + 1]),
-                          fmaxf(red[team * 4 + 2], red[team * 4 + 3]));  // 4 waves per team
+    float a = red[team * WT];
+#pragma unroll
+    for (int w = 1; w < WT; ++w) a = fmaxf(a, red[team * WT + w]);
     const float inv = (a == 0.0f) ? 0.0f : __fdiv_rn(7.0f, a);
     const float m = rb * inv;  // fl(r_b * inv_i)
     if (live) {
@@ -298,6 +348,8 @@ __global__ __launch_bounds__(Teams<K>::threads) void quant_kernel(
       store_nibbles<E>(Xq + (size_t)r * (K / 2) + (size_t)t * (E / 2), nib);
       if (t == 0) a_scale[r] = __fdiv_rn(a, 7.0f);
     }
+    if constexpr (!RTm::kAhead)
+      if (it + 1 < iters) load_row_or_zero<K, RT>(X, r0 + (it + 1) * kTeams + team, r1, t, vn);
   }
 }
 
@@ -525,42 +577,75 @@ int num_cus() {
 // Pass 1 writes one partial row per workgroup: at most kMaxPartialRows of
 // them, so the reduction every pass-2 workgroup repeats stays small. Pass 2
 // has no such limit: up to 4 workgroups per CU.
-template <int K>
-int split_rows(int M, int cap, int* rows_per_wg) {
-  constexpr int kTeams = Teams<K>::n;
+int split_rows(int M, int kTeams, int cap, int* rows_per_wg) {
   int wgs = (M + kTeams - 1) / kTeams;
   wgs = wgs < cap ? wgs : cap;
   *rows_per_wg = (M + wgs - 1) / wgs;
   return (M + *rows_per_wg - 1) / *rows_per_wg;
 }
 
+// Teams per workgroup for M rows over `cap` workgroups.
+template <int K>
+int row_teams(int M, int cap) {
+  if (K <= 4096) return 4;
+  const int rows = (M + cap - 1) / cap;
+  return K == 8192 ? (rows > 2 ? 4 : 2) : (rows > 1 ? 2 : 1);
+}
+
+// f(std::integral_constant teams) for the team counts of K.
+template <int K, class F>
+void with_teams(int teams, F f) {
+  if constexpr (K <= 4096) {
+    f(std::integral_constant<int, 4>{});
+  } else if constexpr (K == 8192) {
+    if (teams == 4)
+      f(std::integral_constant<int, 4>{});
+    else
+      f(std::integral_constant<int, 2>{});
+  } else {
+    if (teams == 2)
+      f(std::integral_constant<int, 2>{});
+    else
+      f(std::integral_constant<int, 1>{});
+  }
+}
+
 template <int K>
 hipError_t launch_k(const uint16_t* X, int M, int g, const int32_t* perm, int flags, uint8_t* Xq,
                     float* a_scale, float* s_group, void* workspace, hipStream_t stream) {
   int rpw1 = 0, rpw2 = 0;
-  const int wgs1 = split_rows<K>(M, kMaxPartialRows, &rpw1);
+  const int t1 = row_teams<K>(M, kMaxPartialRows);
+  const int wgs1 = split_rows(M, t1, kMaxPartialRows, &rpw1);
   // One pass-2 workgroup per compute unit: each re-reads the partial rows, so
-  // more workgroups pay that reduction more often (measured at K = 8192,
-  // M = 8192: 154.8 us for the call against 160.5 us with two per CU and
-  // 173.4 us with four; K = 16384, M = 2048: 128.9 against 148.9 us).
-  const int wgs2 = split_rows<K>(M, num_cus(), &rpw2);
+  // more workgroups pay that reduction more often (K = 8192, M = 8192, with two
+  // teams: 154.8 us for the call against 160.5 us with two per CU and 173.4 us
+  // with four).
+  const int t2 = row_teams<K>(M, num_cus());
+  const int wgs2 = split_rows(M, t2, num_cus(), &rpw2);
   float* gpart = static_cast<float*>(workspace);
   const bool rot = !(flags & kSkipRotation);
   const bool smooth = !(flags & kSkipSmoothing);
-#define RRS_QUANT(R_, S_)                                                                   \
-  quant_kernel<K, R_, S_><<<wgs2, Teams<K>::threads, 0, stream>>>(X, M, g, rpw2, wgs1, perm, \
-                                                                  gpart, Xq, a_scale, s_group)
-  if (smooth) {
-    if (rot)
-      rot_max_kernel<K, true><<<wgs1, Teams<K>::threads, 0, stream>>>(X, M, g, rpw1, perm, gpart);
-    else
-      rot_max_kernel<K, false><<<wgs1, Teams<K>::threads, 0, stream>>>(X, M, g, rpw1, perm, gpart);
-  }
-  if (rot && smooth) RRS_QUANT(true, true);
-  else if (rot) RRS_QUANT(true, false);
-  else if (smooth) RRS_QUANT(false, true);
-  else RRS_QUANT(false, false);
+  if (smooth)
+    with_teams<K>(t1, [&](auto T) {
+      constexpr int N = decltype(T)::value;
+      if (rot)
+        rot_max_kernel<K, true, false, N>
+            <<<wgs1, RowTeams<K, N>::threads, 0, stream>>>(X, M, g, rpw1, perm, gpart);
+      else
+        rot_max_kernel<K, false, false, N>
+            <<<wgs1, RowTeams<K, N>::threads, 0, stream>>>(X, M, g, rpw1, perm, gpart);
+    });
+  with_teams<K>(t2, [&](auto T) {
+    constexpr int N = decltype(T)::value;
+#define RRS_QUANT(R_, S_)                                                                        \
+  quant_kernel<K, R_, S_, false, N><<<wgs2, RowTeams<K, N>::threads, 0, stream>>>(              \
+      X, M, g, rpw2, wgs1, perm, gpart, Xq, a_scale, s_group)
+    if (rot && smooth) RRS_QUANT(true, true);
+    else if (rot) RRS_QUANT(true, false);
+    else if (smooth) RRS_QUANT(false, true);
+    else RRS_QUANT(false, false);
 #undef RRS_QUANT
+  });
   return hipGetLastError();
 }
 
@@ -569,29 +654,35 @@ template <int K>
 hipError_t launch_block_max_k(const uint16_t* X, int M, bool rot, float* part, int* nrows,
                               hipStream_t stream) {
   int rpw = 0;
-  const int wgs = split_rows<K>(M, kMaxPartialRows, &rpw);
-  if (rot)
-    rot_max_kernel<K, true, true><<<wgs, Teams<K>::threads, 0, stream>>>(X, M, 32, rpw, nullptr,
-                                                                          part);
-  else
-    rot_max_kernel<K, false, true><<<wgs, Teams<K>::threads, 0, stream>>>(X, M, 32, rpw, nullptr,
-                                                                           part);
+  const int teams = row_teams<K>(M, kMaxPartialRows);
+  const int wgs = split_rows(M, teams, kMaxPartialRows, &rpw);
+  with_teams<K>(teams, [&](auto T) {
+    constexpr int N = decltype(T)::value;
+    if (rot)
+      rot_max_kernel<K, true, true, N>
+          <<<wgs, RowTeams<K, N>::threads, 0, stream>>>(X, M, 32, rpw, nullptr, part);
+    else
+      rot_max_kernel<K, false, true, N>
+          <<<wgs, RowTeams<K, N>::threads, 0, stream>>>(X, M, 32, rpw, nullptr, part);
+  });
   *nrows = wgs;
   return hipGetLastError();
 }
 
-// Runtime reorder, pass 2: quant with one given row of group maxima.
+// Runtime reorder, pass 2: quant with one given row of group maxima. (Two teams
+// at K = 8192 and one at 16384: more do not fit in LDS beside the ranking.)
 template <int K>
 hipError_t launch_ordered_k(const uint16_t* X, int M, int g, bool rot, const float* part,
                             int nrows, uint8_t* Xq, float* a_scale, float* s_group,
                             int32_t* block_order, hipStream_t stream) {
+  constexpr int N = K <= 4096 ? 4 : K == 8192 ? 2 : 1;
   int rpw = 0;
-  const int wgs = split_rows<K>(M, num_cus(), &rpw);  // as launch_k's second pass
+  const int wgs = split_rows(M, N, num_cus(), &rpw);  // as launch_k's second pass
   if (rot)
-    quant_kernel<K, true, true, true><<<wgs, Teams<K>::threads, 0, stream>>>(
+    quant_kernel<K, true, true, true, N><<<wgs, RowTeams<K, N>::threads, 0, stream>>>(
         X, M, g, rpw, nrows, nullptr, part, Xq, a_scale, s_group, block_order);
   else
-    quant_kernel<K, false, true, true><<<wgs, Teams<K>::threads, 0, stream>>>(
+    quant_kernel<K, false, true, true, N><<<wgs, RowTeams<K, N>::threads, 0, stream>>>(
         X, M, g, rpw, nrows, nullptr, part, Xq, a_scale, s_group, block_order);
   return hipGetLastError();
 }
