@@ -19,13 +19,16 @@
 // every product stays inside one group.
 //
 // Measured in the kernel alone, back to back, cold weights, g = 128, row-major
-// (tiled), before -> now: 173 x 4096 x 4096 (M x K x N) 35.0 -> 11.8 us; 80 x
-// 4096 x 4096 34.6 -> 8.8 (6.5); 300 x 8192 x 1024 62.5 -> 14.0 (9.8); 128 x
-// 8192 x 8192 63.9 -> 19.2 (14.7); 100 x 4096 x 12288 35.6 -> 19.3, where the
-// main kernel served; 49 x 4096 x 22016 22.9 -> 19.8 (20.6 -> 15.2); 32 x 8192 x
-// 28672 29.8 -> 26.5 (28.7 -> 20.3), where few-token kernels did. Four waves
-// beat eight on one tile (11.8 against 12.4 us at 173 x 4096 x 4096: the sum
-// of eight takes longer), and loads four tiles ahead do not fit the registers.
+// (tiled), before -> now: 173 x 4096 x 4096 (M x K x N) 35.0 -> 11.1 us (8.7); 64 x
+// 4096 x 4096 12.1 -> 7.1 (5.4); 300 x 8192 x 1024 62.5 -> 13.2 (9.8); 128 x 8192 x
+// 8192 63.9 -> 18.2 (13.9); 100 x 4096 x 12288 35.6 -> 19, where the main kernel
+// served; 49 x 4096 x 22016 22.9 -> 19.0 (20.6 -> 15.0); 32 x 8192 x 28672 29.8 -> 26
+// (28.7 -> 20), where few-token kernels did. At 173 x 4096 x 4096 a wave issues in
+// half of its clocks; four waves beat eight on one tile (11.8 against 12.4 us: the
+// sum of eight takes longer), loads four tiles ahead are slower even with registers
+// for them (12.5 us at one workgroup per compute unit), and so are tiles of 32
+// columns (16.0: the tokens are read twice as often). The last trip's loads past
+// the end cost 6 to 12 % and are left out.
 //
 // Codes are unpacked into the high nibble of each int8 lane (16 q), the 2^-8
 // folded into the output scale, and a group's accumulators start from the bits
@@ -240,15 +243,27 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
     load_b(d, d);
     load_a(d, d);
   }
-  // Tiles past a wave's last load its last one again and count with scale 0.
+  // Trips of U tiles; the last one requests nothing past itself. Tiles past a
+  // wave's last repeat it and count with scale 0.
   constexpr int U = TPG > DB ? TPG : DB;
-  for (int i0 = 0; i0 < n; i0 += U) {
+  int i0 = 0;
+  for (; i0 + U < n; i0 += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       compute(u, i0 + u);
       load_b(u % DB, i0 + u + DB);
       load_a(u % DB, i0 + u + DB);
       __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (n > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      compute(u, i0 + u);
+      if (u + DB < U) {
+        load_b(u % DB, i0 + u + DB);
+        load_a(u % DB, i0 + u + DB);
+      }
     }
   }
   if constexpr (mode == kPartials) return;
@@ -296,10 +311,10 @@ hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
 // Token blocks per tile: the largest tile that still gives 160 workgroups (a
 // little over half of the compute units; below that a smaller tile's second
 // pass over the weights, out of L2, costs less than the idle units). Measured,
-// row-major, 64 / 32 / 16 tokens per tile: 300 x 8192 x 1024 18.4 / 14.0 / 21.6
-// us (80 / 160 / 304 workgroups); 64 x 4096 x 4096 11.2 / 8.9 / 7.6 (64 / 128 /
-// 256); 32 x 16384 x 4096 - / 24.2 / 20.8 (64 / 128); 20 x 4096 x 12288 - / 8.5 /
-// 13.1 (192 / 384); 173 x 4096 x 4096 11.8 / 14.8 (192 / 384).
+// row-major, 64 / 32 / 16 tokens per tile: 300 x 8192 x 1024 17.2 / 13.2 / 20.0
+// us (80 / 160 / 304 workgroups); 64 x 4096 x 4096 10.5 / 8.1 / 7.1 (64 / 128 /
+// 256); 32 x 16384 x 4096 - / 24.2 / 20.8 (64 / 128); 32 x 4096 x 12288 - / 8.4 /
+// 11.4 (192 / 384); 173 x 4096 x 4096 11.1 / 13.9 / 16.1 (192 / 384 / 704).
 int token_blocks(int M, int N) {
   const int tn = (N + BN - 1) / BN;
   for (int rb = 4; rb > 1; rb /= 2) {
@@ -342,7 +357,7 @@ hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_gr
 // 64 costs about 1 us per 1000 K tiles of 128 over the whole chip, a round of
 // 256 large ones 1 us per K tile. Measured, here / main: 512 x 8192 x 8192
 // (1024 small tiles, one round) 63.1 / 64.4 us; 512 x 4096 x 12288 (1536, one
-// round) 53.1 / 39.6; 256 x 4096 x 4096 (256, one round) 11.8 / 33.2.
+// round) 53.1 / 39.6; 256 x 4096 x 4096 (256, one round) 10.8 / 33.2.
 bool mid_kernel_fits(int M, int N) {
   if (M <= 16) return false;
   const long small = (long)((M + 63) / 64) * ((N + 63) / 64);
