@@ -124,11 +124,21 @@ def _check(code: int, where: str) -> None:
         raise RRSError(code, where)
 
 
+# The handle of a device's current stream without building a Stream object (0.2 us
+# instead of 2 us per call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device: torch.device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _dev(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Tuple[int, ...]) -> int:
+    if (type(t) is torch.Tensor and t.is_cuda and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous()):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -186,8 +196,8 @@ def rotate_smooth_quant(X: torch.Tensor, g: int, perm: Optional[torch.Tensor] = 
         s = torch.empty((max(K // g, 1),), dtype=torch.float32, device=X.device)
     else:
         Xq, a, s = out
-    nbytes = workspace_bytes(M, K, g)
     if workspace is None:
+        nbytes = workspace_bytes(M, K, g)
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     _check(lib().rrs_rotate_smooth_quant_ex(
         xp, M, K, g, _perm_ptr(perm, K), flags, Xq.data_ptr(), a.data_ptr(), s.data_ptr(),
@@ -223,8 +233,8 @@ def linear(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
     xp = _dev(X, "X", torch.float16, (M, K))
     wqp = _dev(Wq, "Wq", torch.uint8, (N, K // 2))
     wsp = _dev(w_scale, "w_scale", torch.float32, (N,))
-    nbytes = linear_workspace_bytes(M, K, g)
     if workspace is None:
+        nbytes = linear_workspace_bytes(M, K, g)
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
@@ -407,8 +417,8 @@ def rotate_smooth_quant_reorder(X: torch.Tensor, g: int, workspace: Optional[tor
         order = torch.empty((max(K // REORDER_BLOCK, 1),), dtype=torch.int32, device=X.device)
     else:
         Xq, a, s, order = out
-    nbytes = reorder_workspace_bytes(M, K, g)
     if workspace is None:
+        nbytes = reorder_workspace_bytes(M, K, g)
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     _check(lib().rrs_rotate_smooth_quant_reorder(
         xp, M, K, g, flags, Xq.data_ptr(), a.data_ptr(), s.data_ptr(), order.data_ptr(),
@@ -445,8 +455,8 @@ def linear_reorder(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: 
     xp = _dev(X, "X", torch.float16, (M, K))
     wqp = _dev(Wq, "Wq", torch.uint8, (N, K // 2))
     wsp = _dev(w_scale, "w_scale", torch.float32, (N,))
-    nbytes = linear_reorder_workspace_bytes(M, K, g)
     if workspace is None:
+        nbytes = linear_reorder_workspace_bytes(M, K, g)
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))

@@ -158,18 +158,18 @@ rrs_status debug_check_finite_f32(const float* p, size_t count, const char* what
 std::atomic<int> g_arch_cache[kMaxDevices];
 
 rrs_status check_device() {
-  int count = 0;
-  if (hipGetDeviceCount(&count) != hipSuccess || count <= 0) {
-    (void)hipGetLastError();
-    return RRS_ERR_NO_DEVICE;
-  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();
     return RRS_ERR_NO_DEVICE;
   }
   int cached = (dev >= 0 && dev < kMaxDevices) ? g_arch_cache[dev].load() : 0;
-  if (cached == 0) {
+  if (cached == 0) {  // the first call on this device
+    int count = 0;
+    if (hipGetDeviceCount(&count) != hipSuccess || count <= 0) {
+      (void)hipGetLastError();
+      return RRS_ERR_NO_DEVICE;
+    }
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) {
       (void)hipGetLastError();
