@@ -494,7 +494,9 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
  * token codes can first be written out in the matrix instruction's operand
  * order (0.82 bytes per code). The functions below are the ones of the same
  * names without "_scratch" plus a scratch buffer for that: same arguments,
- * checks and results (Y bit for bit). scratch may be NULL or smaller than
+ * checks and results (Y up to the order of its f32 sum over the groups: the same
+ * bits where one team of waves takes all of K, a float16 step here and there in
+ * mid-size calls where two share it). scratch may be NULL or smaller than
  * rrs_gemm_scratch_bytes: the call then runs as the plain function does. It
  * must be 16-byte aligned, its contents before and after are undefined, and
  * calls that may overlap need a scratch buffer each.

@@ -1,8 +1,9 @@
 // W4A4 GEMM with Runtime Smooth for many tokens on the 6-bit matrix rate: the
 // same product as the main kernel (Section 3.2, Eq. 3, Fig. 4 step (3)),
 //   Y[i, n] = fp16( alpha_i * beta_n / K * sum_b s_b * P_b[i, n] ),
-// and the same bits: the partials P_b are exact here too, and each is added with
-// one FMA by s_b in the same order.
+// and, with one team of waves, the same bits: the partials P_b are exact here too,
+// and each is added with one FMA by s_b in the same order. Two teams (split_teams)
+// sum the two halves of K apart and add the two sums last.
 //
 // What bounds the int8 kernel is issue: per 32 x 32 x 64 of work two MFMAs (64
 // clocks) and 20.5 vector instructions (82 clocks), of which 16 rescale (an
@@ -156,9 +157,10 @@ struct Shape {
 
 // GS = g / 32. kPerChannel: one sum over all of K and no rescale (Section 2.1).
 // kGather (runtime channel reorder): position block p of the tokens pairs with
-// block border[p] of every Wq row.
-template <int GS, int WMC, bool kPerChannel, bool kGather, bool kTiled>
-__global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
+// block border[p] of every Wq row. KS = 2: two teams of 2 WMC waves on one tile,
+// each over half of K.
+template <int GS, int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
+__global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
     const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
     const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
     const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
@@ -170,14 +172,20 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   constexpr bool kKeep = kPerChannel || GS > 4;  // a sum spans several K tiles
   constexpr int GPT = GS >= 4 ? 1 : 4 / GS;      // groups per K tile
   constexpr int TPG = GS >= 4 ? GS / 4 : 1;      // K tiles per group
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * S::STAGE];
+  __shared__ __attribute__((aligned(16))) uint8_t lds_all[KS * 2 * S::STAGE];
   __shared__ float scale_tab[BM + BN];  // alpha of the tile's rows, then beta of its columns
   __shared__ int btab[kGather ? 16384 / kReorderBlock : 1];
 
   const TileMap tile = map_tile<BM, BN>(M, N);
   if (!tile.valid) return;
   const int m0 = tile.m0, n0 = tile.n0;
-  const int t = threadIdx.x;
+  // The team's share: its threads, its LDS and its K tiles, [k0, k0 + nt).
+  const int team = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+  const int t = threadIdx.x & (kThreads - 1);
+  const int ntiles = K / 128;
+  const int nt = ntiles / KS;
+  const int k0 = team * nt;
+  uint8_t* const lds = lds_all + team * 2 * S::STAGE;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave % WMC;
@@ -188,16 +196,16 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   // blocks. Weights: thread t handles piece q (32 channels) of rows t / 4 +
   // kRowsPer i. Rows past M or N take the last valid block or row instead: their
   // results are never stored.
-  const int ntiles = K / 128;
   const int nblk = (int)token_blocks(M);
   const int q = t & 3;
   const int row0 = t >> 2;
   constexpr uint32_t wts = (uint32_t)lay.tile();
   constexpr uint32_t wqs = (uint32_t)lay.quarter();
   const uint32_t bstep = (uint32_t)ntiles * kTokTile;  // bytes of one 32-row block
-  const uint8_t* abase = Xe + (size_t)(m0 >> 5) * bstep;
-  const uint8_t* sbase = Xe + (size_t)nblk * bstep + (size_t)(m0 >> 5) * ntiles * kTokSum;
-  const uint8_t* bbase = Wq + lay.row(n0, K);
+  const uint8_t* abase = Xe + (size_t)(m0 >> 5) * bstep + (size_t)k0 * kTokTile;
+  const uint8_t* sbase =
+      Xe + (size_t)nblk * bstep + ((size_t)(m0 >> 5) * ntiles + k0) * kTokSum;
+  const uint8_t* bbase = Wq + lay.row(n0, K) + (kGather ? 0 : (size_t)k0 * wts);
   const int lastb = nblk - 1 - (m0 >> 5);
   uint32_t aoff[S::PA], boff_[S::PB];
 #pragma unroll
@@ -225,7 +233,8 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   int a8b = a8 + 512, b8b = b8 + 2 * kSec8;
   asm volatile("" : "+v"(a8b), "+v"(b8b));
   const int sa_rd = S::SA + (wm * 64 + lane) * 4;
-  const uint8_t* dbase = Xe + (size_t)min((m0 >> 5) + wm * 2 + 1, nblk - 1) * bstep;
+  const uint8_t* dbase = Xe + (size_t)min((m0 >> 5) + wm * 2 + 1, nblk - 1) * bstep +
+                         (size_t)k0 * kTokTile;
   uint32_t d16 = lane * 16, d8 = lane * 8;
 
   // A uniform pointer, opaque so that the loads keep it in scalar registers, and
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   uint32_t rs;
   auto boff = [&](int kt) -> uint32_t {
     if constexpr (kGather) {
-      const uint32_t p = (uint32_t)btab[kt * 4 + q];
+      const uint32_t p = (uint32_t)btab[(k0 + kt) * 4 + q];
       return (p >> 2) * wts + (p & 3u) * wqs;
     } else {
       return (uint32_t)kt * wts;
@@ -356,11 +365,11 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   auto col_of = [&](int j) { return (wn * NB + j) * 32 + lr; };
 
   // Prologue: the output scales in LDS, tile 0 staged, tile 1 in flight.
-  for (int i = t; i < BM + BN; i += kThreads)
+  for (int i = threadIdx.x; i < BM + BN; i += KS * kThreads)
     scale_tab[i] = i < BM ? a_scale[min(m0 + i, M - 1)] : w_scale[min(n0 + i - BM, N - 1)];
   if constexpr (kGather) {
     // Entries are masked into range, so any table keeps every load in bounds.
-    for (int i = t; i < K / kReorderBlock; i += kThreads)
+    for (int i = threadIdx.x; i < K / kReorderBlock; i += KS * kThreads)
       btab[i] = border[i] & (K / kReorderBlock - 1);
     __syncthreads();
   }
@@ -385,10 +394,12 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
   constexpr int kBar = NB;                 // the barrier stands before this block
   constexpr int kChunk = 64 * TPG / GPT;   // K tiles whose scales one register holds
 
-  for (int kc = 0; kc < ntiles; kc += kChunk) {
+  const int ngrp = nt * 128 / (GS * 32);
+  for (int kc = 0; kc < nt; kc += kChunk) {
     float sv = 0.0f;
-    if constexpr (!kPerChannel) sv = s_group[min(kc / TPG * GPT + lane, K / (GS * 32) - 1)];
-    const int kend = min(kc + kChunk, ntiles);
+    if constexpr (!kPerChannel)
+      sv = s_group[team * ngrp + min(kc / TPG * GPT + lane, ngrp - 1)];
+    const int kend = min(kc + kChunk, nt);
     for (int kt0 = kc; kt0 < kend; kt0 += 2) {
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
@@ -410,7 +421,7 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
           if (b == kBar) __syncthreads();
           if (b == 0) {
             read_b(p, 1);
-            read_d(p ^ 1, min(kt + 1, ntiles - 1));
+            read_d(p ^ 1, min(kt + 1, nt - 1));
           }
           if (b == kBar) {
             read_a(p ^ 1);
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
           // The next tile is staged before the barrier, each part's registers
           // refilled at once.
           auto steps = [&](int part) {
-            const int kn = min(kt + 2, ntiles - 1);
+            const int kn = min(kt + 2, nt - 1);
             if (b == 0 && part == 0) {
               if constexpr (kGather) bnext = boff(kn);
               stage_a(p ^ 1);
@@ -487,6 +498,39 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
         for (int r = 0; r < 16; ++r) f[h][j][r] = pk[h][j][r];
   }
 
+  // Two teams: each hands the half of the rows that it does not store (the upper
+  // blocks, if it is the second) to the other through LDS, and adds what it gets.
+  if constexpr (KS == 2) {
+    __syncthreads();
+    float4* const xch = reinterpret_cast<float4*>(lds_all);
+    constexpr int kWave = NB * 4 * 64;  // float4s per wave
+    static_assert(2 * 2 * WMC * kWave * 16 <= KS * 2 * S::STAGE, "the exchange fits");
+    auto give = [&](const float (&x)[NB][16]) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+          xch[(team * 2 * WMC + wave) * kWave + (j * 4 + r / 4) * 64 + lane] =
+              make_float4(x[j][r], x[j][r + 1], x[j][r + 2], x[j][r + 3]);
+    };
+    auto take = [&](float (&x)[NB][16]) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4) {
+          const float4 o =
+              xch[((team ^ 1) * 2 * WMC + wave) * kWave + (j * 4 + r / 4) * 64 + lane];
+          x[j][r] += o.x;
+          x[j][r + 1] += o.y;
+          x[j][r + 2] += o.z;
+          x[j][r + 3] += o.w;
+        }
+    };
+    if (team == 0) give(f[1]); else give(f[0]);
+    __syncthreads();
+    if (team == 0) take(f[0]); else take(f[1]);
+  }
+
   // The products are in units of 1/64, and out_scale also undoes the 16 x 16 of
   // the int8 kernels' operands: 2^6 * 2^8, exact.
   const float inv = out_scale * 16384.0f;
@@ -502,7 +546,8 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
       const int col = n0 + col_of(j);
       const float bc = scale_tab[BM + col_of(j)];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < 2; ++h) {
+        if (KS == 2 && h != team) continue;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m0 + row_of(h, r);
@@ -512,6 +557,7 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
               __builtin_bit_cast(uint16_t, (_Float16)((f[h][j][r] * (ar * inv)) * bc));
           if (decltype(full)::value || (row < M && col < N)) Y[(size_t)row * N + col] = v;
         }
+      }
     }
   };
   if (m0 + BM <= M && n0 + BN <= N)
@@ -520,7 +566,7 @@ __global__ __launch_bounds__(128 * WMC, 2) void gemm_fp6_kernel(
     store(std::false_type{});
 }
 
-template <int WMC, bool kPerChannel, bool kGather, bool kTiled>
+template <int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
 hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_group,
                        const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
                        uint16_t* Y, float out_scale, hipStream_t stream, const int32_t* border) {
@@ -529,8 +575,8 @@ hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_g
   const int grid = 8 * ((T + 7) / 8);
 #define RRS_FP6(G_)                                                                        \
   case G_:                                                                                 \
-    gemm_fp6_kernel<G_ / 32, WMC, kPerChannel, kGather, kTiled>                            \
-        <<<grid, S::kThreads, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,  \
+    gemm_fp6_kernel<G_ / 32, WMC, KS, kPerChannel, kGather, kTiled>                        \
+        <<<grid, KS * S::kThreads, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,  \
                                            out_scale, border);                             \
     break
   if constexpr (kPerChannel) {
@@ -550,28 +596,42 @@ hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_g
   return hipGetLastError();
 }
 
-// Time of one K tile of 128 for the whole product, in ns: a round of 256 tiles of
-// 256 x 128 takes 780, one of 512 tiles of 128 x 128 (two per compute unit) 890,
-// a last round of up to 256 of those (one per unit) 620. Measured: 2048 x K x
-// 12288 (768 / 1536 tiles) 2.34 / 2.67 us per K tile, 512 x 8192 x 8192 (128 /
-// 256 tiles) 51.7 / 45 us.
-int tile_ns(int M, int N, int* wmc) {
+// At most 256 tiles of 128 x 128: one per compute unit, whose two waves per SIMD
+// then are two teams, each over half of K. A compute unit with one team per tile ran
+// one wave per SIMD. GEMM with the token pass, one team / two: 512 x 8192 x 8192
+// 47.5 -> 38.7 us; 777 x 16384 x 4096, g = 256 76 -> 63; 1000 x 4096 x 4096, g = 64
+// 36 -> 28; 512 x 2048 x 8192 17.0 -> 15.5; at K = 1024 12.2 both. With more tiles
+// the teams only share one barrier that two workgroups would not (2048 x 4096 x
+// 12288 98 -> 108).
+bool split_teams(int M, int N, int K) {
+  return (long)((M + 127) / 128) * ((N + 127) / 128) <= 256 && K >= 2048;
+}
+
+// Otherwise 256 x 128 or 128 x 128, by the time of one K tile of 128 for the whole
+// product, in ns: a round of 256 tiles of 256 x 128 takes 780, one of 512 tiles of
+// 128 x 128 (two per compute unit) 890, a last round of up to 256 of those (one
+// per unit) 620. Measured: 2048 x K x 12288 (768 / 1536 tiles) 2.34 / 2.67 us per
+// K tile, 512 x 8192 x 8192 (128 / 256 tiles) 51.7 / 45 us in all.
+bool small_tiles(int M, int N) {
   const long tn = (N + 127) / 128;
   const long t256 = (long)((M + 255) / 256) * tn, t128 = (long)((M + 127) / 128) * tn;
   const long large = (t256 + 255) / 256 * 780;
   const long rest = t128 % 512;
-  const long small = t128 / 512 * 890 + (rest == 0 ? 0 : rest <= 256 ? 620 : 890);
-  *wmc = small < large ? 2 : 4;
-  return (int)(small < large ? small : large);
+  return t128 / 512 * 890 + (rest == 0 ? 0 : rest <= 256 ? 620 : 890) < large;
 }
 
 }  // namespace
 
-// Where the main kernel would serve, whose bits this one reproduces (so a call
-// gives the same Y with and without scratch); the token pass is a small part of
-// every such call. The scratch stays below 1 GB.
+// Where the main kernel would serve; with two teams also from 512 tiles of 64 x 64 of
+// the mid-size kernel on (mid-size -> this one, token pass included: 256 x 8192 x
+// 8192, 512 tiles, 33 us both; 640 tiles: 320 x 4096 x 8192 26 -> 22, 128 x 4096 x
+// 20480 27 -> 21; 768 tiles: 384 x 8192 x 8192 46 -> 34, 768 x 16384 x 4096 87 ->
+// 60; below: 384 x 4096 x 4096, 384 tiles, 18.5 -> 20.7). The scratch stays below
+// 1 GB.
 size_t fp6_scratch_bytes(int M, int N, int K) {
-  if (M <= 16 || mid_kernel_fits(M, N)) return 0;
+  if (M <= 16) return 0;
+  const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+  if (mid_kernel_fits(M, N) && !(split_teams(M, N, K) && tiles64 > 512)) return 0;
   const size_t n = expanded_bytes(M, K);
   return n <= ((size_t)1 << 30) ? n : 0;
 }
@@ -585,19 +645,22 @@ hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const f
   expand_tokens_kernel<<<groups, 256, 0, stream>>>(Xq, M, K, Xe);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  int wmc;
-  tile_ns(M, N, &wmc);
+  const bool teams = split_teams(M, N, K);
+  const bool small = teams || small_tiles(M, N);
 #define RRS_ARGS \
   Xe, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale, stream, border
-#define RRS_FORM(PC_, GA_)                                                                   \
-  return wmc == 4 ? (lay.tiled ? launch_gemm<4, PC_, GA_, true>(RRS_ARGS)                    \
-                               : launch_gemm<4, PC_, GA_, false>(RRS_ARGS))                  \
-                  : (lay.tiled ? launch_gemm<2, PC_, GA_, true>(RRS_ARGS)                    \
-                               : launch_gemm<2, PC_, GA_, false>(RRS_ARGS))
+#define RRS_LAY(WMC_, KS_, PC_, GA_)                                       \
+  (lay.tiled ? launch_gemm<WMC_, KS_, PC_, GA_, true>(RRS_ARGS)            \
+             : launch_gemm<WMC_, KS_, PC_, GA_, false>(RRS_ARGS))
+#define RRS_FORM(PC_, GA_)                                                 \
+  return teams   ? RRS_LAY(2, 2, PC_, GA_)                                 \
+         : small ? RRS_LAY(2, 1, PC_, GA_)                                 \
+                 : RRS_LAY(4, 1, PC_, GA_)
   if (!s_group) RRS_FORM(true, false);
   if (border) RRS_FORM(false, true);
   RRS_FORM(false, false);
 #undef RRS_FORM
+#undef RRS_LAY
 #undef RRS_ARGS
 }
 

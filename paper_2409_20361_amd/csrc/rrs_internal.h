@@ -156,7 +156,8 @@ hipError_t launch_w4a4_gemm_mid_partials(const uint8_t* Xq, const uint8_t* Wq, i
                                          int g, int32_t* P, hipStream_t stream);
 
 // Many tokens on the 6-bit matrix rate (rrs_gemm_fp6.hip), with scratch memory of
-// the caller for the spread token codes: the main kernel's results bit for bit.
+// the caller for the spread token codes: the main kernel's results, bit for bit
+// where one team of waves takes all of K.
 // fp6_scratch_bytes is 0 where another kernel serves. s_group == nullptr:
 // per-channel (border must be nullptr too).
 size_t fp6_scratch_bytes(int M, int N, int K);

@@ -1,6 +1,8 @@
 """The many-token GEMM on scratch memory (6-bit operands) against the entry points
 without scratch (int8 operands): the partials of both are exact and each is
-added with one FMA in the same order, so Y must be the same bits. Codes are all
+added with one FMA in the same order, so Y must be the same bits. (Where two teams
+share a tile the order differs; the second test holds those to the binary64 sum,
+with the bound of the mid-size kernel's test.) Codes are all
 sixteen nibbles, at the edges of the tiles: ragged rows (a last block of 32 rows
 partly or wholly past M) and columns, both tile shapes, every group size (64 at K =
 16384: more groups than one register of scales), both weight layouts, the
@@ -8,6 +10,9 @@ runtime reorder's table and the per-channel scheme. -0 and rounding cannot hide
 anything: the comparison is on the bits."""
 import numpy as np
 import pytest
+
+from tests._gpu_util import tile_wq, to_gpu, to_np
+from tests.test_gemm_mid_gpu import _case, _check, _pack, _partials
 
 pytestmark = pytest.mark.gpu
 
@@ -27,8 +32,8 @@ def _st():
 
 
 CASES = [  # 128 x 128 tiles, then 256 x 128
-    (500, 512, 6208, 128, False), (777, 1024, 4160, 64, True), (770, 16384, 4112, 64, False),
-    (513, 2048, 6176, 512, True),
+    (500, 512, 6208, 128, False), (777, 1024, 4160, 64, True), (500, 16384, 17008, 64, False),
+    (500, 2048, 17008, 512, True),
     (1030, 1024, 5200, 128, True), (1057, 512, 5136, 64, False), (1300, 2048, 6160, 256, False),
     (2049, 1024, 4624, 512, False),
 ]
@@ -68,6 +73,30 @@ def test_scratch_gemm_same_bits(M, K, N, g, tiled):
         torch.cuda.synchronize()
         bits = [t.view(torch.int16) for t in Y]
         assert torch.equal(*bits), f"{form}: {int((bits[0] != bits[1]).sum())} outputs differ"
+
+
+# Two teams: from 513 tiles of 64 x 64 to 256 of 128 x 128, K from 2048.
+TEAMS = [(520, 2048, 4112, 128, False), (577, 2048, 3600, 64, True), (70, 2048, 16400, 512, True),
+         (1000, 4096, 2064, 256, False), (1024, 2048, 4096, 128, True)]
+
+
+@pytest.mark.parametrize("M,K,N,g,tiled", TEAMS)
+def test_two_teams(M, K, N, g, tiled):
+    import paper_2409_20361_amd as rrs
+    print(f"[case] two teams M={M} K={K} N={N} g={g} tiled={tiled}", flush=True)
+    assert rrs.lib().rrs_gemm_scratch_bytes(M, N, K) > 0
+    qx, qw, a, s, b = _case(M, K, N, g, M + K + N)
+    qx[M // 2] = -8
+    qw[:16] = -8
+    dX, dA, dS, dB = to_gpu(_pack(qx)), to_gpu(a), to_gpu(s), to_gpu(b)
+    dW = to_gpu(tile_wq(_pack(qw)) if tiled else _pack(qw))
+    fl = rrs.WEIGHT_TILED if tiled else 0
+    _check(to_np(rrs.w4a4_gemm(dX, dA, dS, dW, dB, g, flags=fl)), _partials(qx, qw, g), a, s, b, K,
+           "plain")
+    order = np.random.default_rng(M).permutation(K // 32).astype(np.int32)
+    qr = qw.reshape(N, K // 32, 32)[:, order].reshape(N, K)
+    _check(to_np(rrs.w4a4_gemm_reorder(dX, dA, dS, dW, dB, to_gpu(order), g, flags=fl)),
+           _partials(qx, qr, g), a, s, b, K, "reorder")
 
 
 def test_scratch_buffer_is_optional():
