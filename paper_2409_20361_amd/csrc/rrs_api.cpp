@@ -407,9 +407,10 @@ rrs_status linear_run(const void* X, const void* Wq, const float* w_scale, int M
     return from_hip(rrs::launch_layer_one_launch(
         static_cast<const uint16_t*>(X), M, N, K, group_size, static_cast<const uint8_t*>(Wq),
         w_scale, static_cast<uint16_t*>(Y), out_scale(K, flags), st, layout(flags)));
+  const rrs::WeightAhead ahead = rrs::weight_ahead(static_cast<const uint8_t*>(Wq), M, N, K);
   hipError_t e = rrs::launch_rotate_smooth_quant(static_cast<const uint16_t*>(X), M, K,
                                                  group_size, perm, flags & kQuantFlags, xq, a,
-                                                 s, qws, st);
+                                                 s, qws, st, ahead);
   if (e != hipSuccess) return RRS_ERR_HIP;
   const rrs_status r = from_hip(run_gemm(xq, a, s, Wq, w_scale, nullptr, M, N, K, group_size,
                                          flags, Y, scratch, scratch_bytes, stream));
@@ -676,9 +677,10 @@ rrs_status rrs_linear_reorder_scratch(const void* X, const void* Wq, const float
   int32_t* order = reinterpret_cast<int32_t*>(ws);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const rrs::WeightAhead ahead = rrs::weight_ahead(static_cast<const uint8_t*>(Wq), M, N, K);
   hipError_t e = rrs::launch_rotate_smooth_quant_reorder(
       static_cast<const uint16_t*>(X), M, K, group_size, flags & RRS_SKIP_ROTATION, xq, a, s,
-      order, qws, st);
+      order, qws, st, ahead);
   if (e != hipSuccess) return RRS_ERR_HIP;
   const rrs_status r = from_hip(run_gemm(xq, a, s, Wq, w_scale, order, M, N, K, group_size, flags,
                                          Y, scratch, scratch_bytes, stream));

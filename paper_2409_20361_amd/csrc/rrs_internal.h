@@ -54,10 +54,19 @@ struct WqLayout {
   }
 };
 
+// Weights that a layer's quantizer reads ahead for the GEMM behind it: column blocks
+// [0, blocks) of 16 rows of Wq (8 K bytes each, in either layout). Only the per-row
+// kernel has compute units to spare for it; the other kernels ignore it.
+struct WeightAhead {
+  const uint8_t* Wq = nullptr;
+  int blocks = 0;
+};
+WeightAhead weight_ahead(const uint8_t* Wq, int M, int N, int K);
+
 hipError_t launch_rotate_smooth_quant(const uint16_t* X, int M, int K, int g,
                                       const int32_t* perm, int flags, uint8_t* Xq,
                                       float* a_scale, float* s_group, void* workspace,
-                                      hipStream_t stream);
+                                      hipStream_t stream, WeightAhead ahead = {});
 
 // One-wave-per-row variant for K <= 4096 (same two passes, same bits).
 hipError_t launch_rotate_smooth_quant_wave(const uint16_t* X, int M, int K, int g,
@@ -235,11 +244,11 @@ bool reorder_one_launch(int M, int K);
 hipError_t launch_reorder_one_launch(const uint16_t* X, int M, int K, int g, bool rot,
                                      uint8_t* Xq, float* a_scale, float* s_group,
                                      int32_t* block_order, void* workspace, hipStream_t stream,
-                                     int extra_rows, int max_polls);
+                                     int extra_rows, int max_polls, WeightAhead ahead = {});
 hipError_t launch_rotate_smooth_quant_reorder(const uint16_t* X, int M, int K, int g, int flags,
                                               uint8_t* Xq, float* a_scale, float* s_group,
                                               int32_t* block_order, void* workspace,
-                                              hipStream_t stream);
+                                              hipStream_t stream, WeightAhead ahead = {});
 // GEMM whose Xq position block p pairs with Wq block border[p].
 hipError_t launch_w4a4_gemm_reorder(const uint8_t* Xq, const float* a_scale,
                                     const float* s_group, const uint8_t* Wq,
@@ -266,7 +275,7 @@ int quant_rows_max(int K, int g);  // rows the per-row kernel takes (no runtime 
 size_t quant_rows_workspace_bytes(int K, int g);
 hipError_t launch_quant_rows(const uint16_t* X, int M, int K, int g, bool rotate, uint8_t* Xq,
                              float* a_scale, float* s_group, void* workspace, hipStream_t stream,
-                             int extra_rows = 0, int max_polls = 0);
+                             int extra_rows = 0, int max_polls = 0, WeightAhead ahead = {});
 // Whether launch_rotate_smooth_quant takes the per-row kernel for this call.
 bool quant_rows_used(int M, int K, int g, const int32_t* perm, int flags);
 // The per-row kernel with the runtime reorder (up to 16 rows, K <= 8192): the
@@ -279,7 +288,7 @@ size_t quant_rows_reorder_workspace_bytes(int K);
 hipError_t launch_quant_rows_reorder(const uint16_t* X, int M, int K, int g, bool rotate,
                                      uint8_t* Xq, float* a_scale, float* s_group,
                                      int32_t* block_order, void* workspace, hipStream_t stream,
-                                     int extra_rows = 0, int max_polls = 0);
+                                     int extra_rows = 0, int max_polls = 0, WeightAhead ahead = {});
 // Waits for `stream` and reports whether the latest one-launch exchange in
 // this workspace (per-row or fused kernel) had a wait that ran out.
 hipError_t quant_exchange_failed(const void* workspace, hipStream_t stream, bool* failed);

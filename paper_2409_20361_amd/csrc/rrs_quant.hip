@@ -779,12 +779,12 @@ hipError_t launch_few_k(const uint16_t* X, int M, int g, const int32_t* perm, bo
 hipError_t launch_rotate_smooth_quant(const uint16_t* X, int M, int K, int g,
                                       const int32_t* perm, int flags, uint8_t* Xq,
                                       float* a_scale, float* s_group, void* workspace,
-                                      hipStream_t stream) {
+                                      hipStream_t stream, WeightAhead ahead) {
   // Up to 16 tokens with smoothing and no static reorder: one workgroup per
   // row, the rows' group maxima exchanged in the workspace (rrs_quant_rows.hip).
   if (quant_rows_used(M, K, g, perm, flags))
     return launch_quant_rows(X, M, K, g, !(flags & kSkipRotation), Xq, a_scale, s_group,
-                             workspace, stream);
+                             workspace, stream, 0, 0, ahead);
   // Few tokens with smoothing: one launch (each workgroup takes the channel
   // maxima of all rows itself).
   if (M <= few_max_rows(K) && !(flags & kSkipSmoothing)) {

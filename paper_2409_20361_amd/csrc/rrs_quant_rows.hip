@@ -33,6 +33,34 @@ namespace {
 constexpr int kMaxRows = 16;      // exchanged words one thread waits for
 constexpr int kMaxRowsWide = 64;  // rows when a group's threads share the reads
 constexpr int kMaxPolls = 1 << 18;
+// Workgroups that read ahead, at most; a multiple of 8. 64 take longer than the rows do (K = 4096,
+// 16 tokens, 24 MB, reorder: 18.7 us; 96 16.2, 120 15.6, 160 15.6, 240 16.0).
+constexpr int kAheadWgs = 160;
+
+// The layer's GEMM starts when this kernel ends, and until then nearly all compute
+// units and the memory are idle: workgroups past the rows read the first column
+// blocks of its weights, which leaves them in L2 and the memory-side cache. A
+// workgroup takes the blocks of its own index modulo 8, which the GEMM's grid deals to
+// the same XCD. They wait for nothing, so the rows' exchange is as without them. At 8
+// tokens, K = 8192, N = 28672 the layer takes 27.6 us instead of 28.9 (20 us of GEMM, whose
+// 117 MB are at 5.9 TB/s; 24 MB are read here).
+template <int K>
+__device__ __forceinline__ void read_ahead(const WeightAhead& ahead, int id, int wgs, int t) {
+  constexpr int kLoads = 8 * K / (16 * kRowThreads);  // 16-byte loads per thread and block
+  constexpr int kBatch = kLoads < 16 ? kLoads : 16;
+  for (int blk = id % wgs; blk < ahead.blocks; blk += wgs) {
+    const uint4* src = reinterpret_cast<const uint4*>(ahead.Wq + (size_t)blk * 8 * K) + t;
+#pragma unroll 1
+    for (int i = 0; i < kLoads; i += kBatch) {
+      uint4 x[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) x[u] = src[(i + u) * kRowThreads];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        asm volatile("" ::"v"(x[u].x), "v"(x[u].y), "v"(x[u].z), "v"(x[u].w));
+    }
+  }
+}
 
 // kReorder (runtime reorder, K <= 8192): the rows exchange their K/32 block
 // maxima instead of their group maxima; every workgroup then ranks the blocks
@@ -51,7 +79,7 @@ template <int K, bool kRot, bool kReorder>
 __global__ __launch_bounds__(kRowThreads) void quant_rows_kernel(
     const uint16_t* __restrict__ X, int M, int g, uint8_t* __restrict__ Xq,
     float* __restrict__ a_scale, float* __restrict__ s_group, int32_t* __restrict__ block_order,
-    uint32_t* header, unsigned long long* tagged, int nrows, int max_polls) {
+    uint32_t* header, unsigned long long* tagged, int nrows, int max_polls, WeightAhead ahead) {
   constexpr int E = FwhtShape<K>::E;  // this thread's channels: t + 256 e after the FWHT
   constexpr int NB = K / kReorderBlock;
   static_assert(!kReorder || NB <= kRowThreads, "one block key per thread");
@@ -69,6 +97,10 @@ __global__ __launch_bounds__(kRowThreads) void quant_rows_kernel(
   __shared__ uint32_t tag_lds;
   const int t = threadIdx.x;
   const int p = blockIdx.x;
+  if (p >= M) {
+    read_ahead<K>(ahead, p, (int)gridDim.x - M, t);
+    return;
+  }
   const int G = K / g;
   const int span = kReorder ? kReorderBlock : g;  // positions per exchanged word
   const int W = K / span;                         // words per row
@@ -236,19 +268,37 @@ __global__ __launch_bounds__(kRowThreads) void quant_rows_kernel(
 template <int K, bool kReorder>
 hipError_t launch_k(const uint16_t* X, int M, int g, bool rotate, uint8_t* Xq, float* a_scale,
                     float* s_group, int32_t* block_order, uint32_t* header,
-                    unsigned long long* tagged, int nrows, int max_polls, hipStream_t stream) {
+                    unsigned long long* tagged, int nrows, int max_polls, WeightAhead ahead,
+                    hipStream_t stream) {
+  const int wgs = ahead.blocks < kAheadWgs ? (ahead.blocks + 7) & ~7 : kAheadWgs;
   if (rotate)
-    quant_rows_kernel<K, true, kReorder><<<M, kRowThreads, 0, stream>>>(
-        X, M, g, Xq, a_scale, s_group, block_order, header, tagged, nrows, max_polls);
+    quant_rows_kernel<K, true, kReorder><<<M + wgs, kRowThreads, 0, stream>>>(
+        X, M, g, Xq, a_scale, s_group, block_order, header, tagged, nrows, max_polls, ahead);
   else
-    quant_rows_kernel<K, false, kReorder><<<M, kRowThreads, 0, stream>>>(
-        X, M, g, Xq, a_scale, s_group, block_order, header, tagged, nrows, max_polls);
+    quant_rows_kernel<K, false, kReorder><<<M + wgs, kRowThreads, 0, stream>>>(
+        X, M, g, Xq, a_scale, s_group, block_order, header, tagged, nrows, max_polls, ahead);
   return hipGetLastError();
 }
 
 }  // namespace
 
 bool quant_rows_fits(int M) { return M >= 1 && M <= kMaxRows; }
+
+// Read ahead for the weight-streaming kernels (up to 16 tokens), as much as fits behind
+// the quantizer's own time, which grows with K: 8 MB at K = 2048 and 8 MB more per
+// doubling. Layer calls, weights cold (us; none, then 16 / 24 / 32 MB): K = 4096, N =
+// 12288, M = 3, 12.96, 12.04 / 12.07 / 12.06; K = 8192, N = 28672, M = 8, 28.9, 28.0 /
+// 27.6 / 27.7; K = 16384, N = 4096, M = 16, 23.6, 22.7 / 22.5 / 21.1; at K = 2048, N =
+// 22016, M = 16 16 MB are too much (15.5, 15.6 / 16.3). At K = 1024 the call is bound by
+// the host and nothing is gained (4 tokens, 10.7). The mid-size kernel, whose weights
+// other compute units read, gains nothing (49 x 4096 x 22016 23.2, 24.1 / 24.3 / 24.4).
+WeightAhead weight_ahead(const uint8_t* Wq, int M, int N, int K) {
+  if (!quant_rows_fits(M) || K < 2048) return {};
+  long mb = 8;
+  for (int k = 2048; k < K; k *= 2) mb += 8;
+  const long most = (mb << 20) / (8 * K);
+  return {Wq, (int)(most < N / 16 ? most : N / 16)};
+}
 
 // Rows the per-row kernel takes at (K, g) without a runtime reorder: 16, or
 // up to 64 where a group's threads share the reads (16 words each). From
@@ -275,7 +325,7 @@ size_t quant_rows_reorder_workspace_bytes(int K) {
 hipError_t launch_quant_rows_reorder(const uint16_t* X, int M, int K, int g, bool rotate,
                                      uint8_t* Xq, float* a_scale, float* s_group,
                                      int32_t* block_order, void* workspace, hipStream_t stream,
-                                     int extra_rows, int max_polls) {
+                                     int extra_rows, int max_polls, WeightAhead ahead) {
   const int nrows = M + extra_rows;  // rows of block maxima the readers wait for
   if (!quant_rows_reorder_fits(M, K) || nrows > kMaxRows) return hipErrorInvalidValue;
   const int polls = max_polls > 0 ? max_polls : kMaxPolls;
@@ -284,7 +334,7 @@ hipError_t launch_quant_rows_reorder(const uint16_t* X, int M, int K, int g, boo
       reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + kQuantHeaderBytes);
 #define RRS_ROWS_R(K_)                                                                          \
   launch_k<K_, true>(X, M, g, rotate, Xq, a_scale, s_group, block_order, header, tagged, nrows, \
-                     polls, stream)
+                     polls, ahead, stream)
   switch (K) {
     case 512: return RRS_ROWS_R(512);
     case 1024: return RRS_ROWS_R(1024);
@@ -298,7 +348,7 @@ hipError_t launch_quant_rows_reorder(const uint16_t* X, int M, int K, int g, boo
 
 hipError_t launch_quant_rows(const uint16_t* X, int M, int K, int g, bool rotate, uint8_t* Xq,
                              float* a_scale, float* s_group, void* workspace, hipStream_t stream,
-                             int extra_rows, int max_polls) {
+                             int extra_rows, int max_polls, WeightAhead ahead) {
   uint32_t* header = static_cast<uint32_t*>(workspace);
   unsigned long long* tagged =
       reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + kQuantHeaderBytes);
@@ -307,7 +357,7 @@ hipError_t launch_quant_rows(const uint16_t* X, int M, int K, int g, bool rotate
   const int polls = max_polls > 0 ? max_polls : kMaxPolls;
 #define RRS_ROWS_K(K_)                                                                   \
   launch_k<K_, false>(X, M, g, rotate, Xq, a_scale, s_group, nullptr, header, tagged, nrows, \
-                      polls, stream)
+                      polls, ahead, stream)
   switch (K) {
     case 512: return RRS_ROWS_K(512);
     case 1024: return RRS_ROWS_K(1024);

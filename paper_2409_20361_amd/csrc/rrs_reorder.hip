@@ -58,10 +58,10 @@ bool reorder_one_launch(int M, int K) { return quant_rows_reorder_fits(M, K) || 
 hipError_t launch_reorder_one_launch(const uint16_t* X, int M, int K, int g, bool rot,
                                      uint8_t* Xq, float* a_scale, float* s_group,
                                      int32_t* block_order, void* workspace, hipStream_t stream,
-                                     int extra_rows, int max_polls) {
+                                     int extra_rows, int max_polls, WeightAhead ahead) {
   if (quant_rows_reorder_fits(M, K))
     return launch_quant_rows_reorder(X, M, K, g, rot, Xq, a_scale, s_group, block_order,
-                                     workspace, stream, extra_rows, max_polls);
+                                     workspace, stream, extra_rows, max_polls, ahead);
   if (!fused_order_fits(M, K)) return hipErrorInvalidValue;
   char* ws = static_cast<char*>(workspace);
   return launch_rotate_smooth_quant_fused_order(
@@ -75,11 +75,11 @@ hipError_t launch_reorder_one_launch(const uint16_t* X, int M, int K, int g, boo
 hipError_t launch_rotate_smooth_quant_reorder(const uint16_t* X, int M, int K, int g, int flags,
                                               uint8_t* Xq, float* a_scale, float* s_group,
                                               int32_t* block_order, void* workspace,
-                                              hipStream_t stream) {
+                                              hipStream_t stream, WeightAhead ahead) {
   const bool rot = !(flags & kSkipRotation);
   if (reorder_one_launch(M, K))
     return launch_reorder_one_launch(X, M, K, g, rot, Xq, a_scale, s_group, block_order,
-                                     workspace, stream, 0, 0);
+                                     workspace, stream, 0, 0, ahead);
   float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                          quant_rows_reorder_workspace_bytes(K));
   int nrows = 0;
