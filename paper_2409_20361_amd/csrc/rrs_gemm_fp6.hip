@@ -70,16 +70,16 @@ struct TileMap {
 
 // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, so
 // each XCD gets a contiguous run of tiles, in column strips of 4 row tiles.
+// Workgroup w, of index `local` on its XCD.
 template <int BM, int BN>
-__device__ __forceinline__ TileMap map_tile(int M, int N) {
+__device__ __forceinline__ TileMap map_tile(int M, int N, int w, int local) {
   const int tm = (M + BM - 1) / BM;
   const int tn = (N + BN - 1) / BN;
   const int T = tm * tn;
-  const int w = blockIdx.x;
   const int per = (T + 7) >> 3;
-  const int lin = (w & 7) * per + (w >> 3);
+  const int lin = (w & 7) * per + local;
   TileMap r;
-  r.valid = lin < T;
+  r.valid = local < per && lin < T;
   const int strip = kGroupM * tn;
   const int first_m = (lin / strip) * kGroupM;
   const int gm = min(tm - first_m, kGroupM);
@@ -160,7 +160,8 @@ struct Shape {
 // block border[p] of every Wq row. KS = 2: two teams of 2 WMC waves on one tile,
 // each over half of K.
 template <int GS, int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
-__global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
+__device__ __forceinline__ void gemm_fp6_tile(
+    const TileMap tile, uint8_t* const lds_all, float* const scale_tab, int* const btab,
     const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
     const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
     const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
@@ -172,12 +173,6 @@ __global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
   constexpr bool kKeep = kPerChannel || GS > 4;  // a sum spans several K tiles
   constexpr int GPT = GS >= 4 ? 1 : 4 / GS;      // groups per K tile
   constexpr int TPG = GS >= 4 ? GS / 4 : 1;      // K tiles per group
-  __shared__ __attribute__((aligned(16))) uint8_t lds_all[KS * 2 * S::STAGE];
-  __shared__ float scale_tab[BM + BN];  // alpha of the tile's rows, then beta of its columns
-  __shared__ int btab[kGather ? 16384 / kReorderBlock : 1];
-
-  const TileMap tile = map_tile<BM, BN>(M, N);
-  if (!tile.valid) return;
   const int m0 = tile.m0, n0 = tile.n0;
   // The team's share: its threads, its LDS and its K tiles, [k0, k0 + nt).
   const int team = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
@@ -566,6 +561,78 @@ __global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
     store(std::false_type{});
 }
 
+template <int GS, int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
+__global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
+    const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
+    const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
+    const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
+    float out_scale, const int32_t* __restrict__ border) {
+  __shared__ __attribute__((aligned(16))) uint8_t stages[KS * 2 * Shape<WMC>::STAGE];
+  __shared__ float scales[Shape<WMC>::BM + Shape<WMC>::BN];
+  __shared__ int order[kGather ? 16384 / kReorderBlock : 1];
+  const int w = blockIdx.x;
+  const TileMap tile = map_tile<Shape<WMC>::BM, Shape<WMC>::BN>(M, N, w, w >> 3);
+  if (!tile.valid) return;
+  gemm_fp6_tile<GS, WMC, KS, kPerChannel, kGather, kTiled>(
+      tile, stages, scales, order, Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,
+      out_scale, border);
+}
+
+// LDS of a tile: the stages, alpha of its rows then beta of its columns, the order.
+template <int WMC, int KS, bool kGather>
+struct Lds {
+  __attribute__((aligned(16))) uint8_t stages[KS * 2 * Shape<WMC>::STAGE];
+  __attribute__((aligned(16))) float scales[Shape<WMC>::BM + Shape<WMC>::BN];
+  int order[kGather ? 16384 / kReorderBlock : 1];
+};
+
+// Tiles of 256 x 128 whose last round would leave half of the compute units or more
+// idle: the tiles of the full rounds (workgroups below `full`) as above, each tile after
+// them as two of 128 x 128 with two teams, which a compute unit finishes in about 0.7 of
+// the time. Quantizer and GEMM, before -> now: 1500 x 4096 x 12288 (576 tiles) 96.3 -> 88.4
+// us, per-channel 84.6 -> 78.5; 2500 x 8192 x 8192, g = 512 (640) 202 -> 190; 2560 x 4096 x
+// 8192, g = 64 (640) 121.8 -> 111.5; 1024 x 4096 x 8704 / 10240 / 11264 (272 / 320 / 352)
+// 65.4 / 64.0 / 62.9 -> 63.2 / 61.4 / 60.9.
+template <int GS, bool kPerChannel, bool kGather, bool kTiled>
+__global__ __launch_bounds__(512, 2) void gemm_fp6_tail_kernel(
+    const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
+    const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
+    const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
+    float out_scale, const int32_t* __restrict__ border, int full) {
+  __shared__ union {
+    Lds<4, 1, kGather> whole;
+    Lds<2, 2, kGather> half;
+  } lds;
+  const int w = blockIdx.x;
+  if (w < full) {
+    const TileMap tile = map_tile<256, 128>(M, N, w, w >> 3);
+    if (!tile.valid) return;
+    gemm_fp6_tile<GS, 4, 1, kPerChannel, kGather, kTiled>(
+        tile, lds.whole.stages, lds.whole.scales, lds.whole.order, Xe, a_scale, s_group, Wq,
+        w_scale, M, N, K, Y, out_scale, border);
+  } else {
+    const int u = (w - full) >> 3;
+    TileMap tile = map_tile<256, 128>(M, N, w, (full >> 3) + (u >> 1));
+    tile.m0 += (u & 1) * 128;
+    if (!tile.valid || tile.m0 >= M) return;
+    gemm_fp6_tile<GS, 2, 2, kPerChannel, kGather, kTiled>(
+        tile, lds.half.stages, lds.half.scales, lds.half.order, Xe, a_scale, s_group, Wq,
+        w_scale, M, N, K, Y, out_scale, border);
+  }
+}
+
+// Tiles of 256 x 128 per XCD, and those of them after its full rounds of 32 where they
+// are split in halves: at most 16, so that the halves take one round; K as split_teams.
+struct TailSplit {
+  int per, tail;
+};
+TailSplit tail_split(int M, int N, int K) {
+  const long T = (long)((M + 255) / 256) * ((N + 127) / 128);
+  const int per = (int)((T + 7) / 8);
+  const int rest = per % 32;
+  return {per, per > 32 && rest <= 16 && K >= 2048 ? rest : 0};
+}
+
 template <int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
 hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_group,
                        const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
@@ -573,8 +640,17 @@ hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_g
   using S = Shape<WMC>;
   const int T = ((M + S::BM - 1) / S::BM) * ((N + S::BN - 1) / S::BN);
   const int grid = 8 * ((T + 7) / 8);
+  const TailSplit sp = WMC == 4 ? tail_split(M, N, K) : TailSplit{0, 0};
+  const int full = 8 * (sp.per - sp.tail);
 #define RRS_FP6(G_)                                                                        \
   case G_:                                                                                 \
+    if constexpr (WMC == 4)                                                                \
+      if (sp.tail) {                                                                       \
+        gemm_fp6_tail_kernel<G_ / 32, kPerChannel, kGather, kTiled>                        \
+            <<<full + 16 * sp.tail, 512, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, \
+                                                      K, Y, out_scale, border, full);      \
+        break;                                                                             \
+      }                                                                                    \
     gemm_fp6_kernel<G_ / 32, WMC, KS, kPerChannel, kGather, kTiled>                        \
         <<<grid, KS * S::kThreads, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,  \
                                            out_scale, border);                             \
@@ -607,15 +683,19 @@ bool split_teams(int M, int N, int K) {
   return (long)((M + 127) / 128) * ((N + 127) / 128) <= 256 && K >= 2048;
 }
 
-// Otherwise 256 x 128 or 128 x 128, by the time of one K tile of 128 for the whole
-// product, in ns: a round of 256 tiles of 256 x 128 takes 780, one of 512 tiles of
-// 128 x 128 (two per compute unit) 890, a last round of up to 256 of those (one
-// per unit) 620. Measured: 2048 x K x 12288 (768 / 1536 tiles) 2.34 / 2.67 us per
-// K tile, 512 x 8192 x 8192 (128 / 256 tiles) 51.7 / 45 us in all.
-bool small_tiles(int M, int N) {
+// Otherwise 256 x 128 or 128 x 128 (also instead of a tail of halves), by the time of
+// one K tile of 128 for the whole product, in ns: a round of 256 tiles of 256 x 128 takes
+// 780, one of 512 tiles of 128 x 128 (two per compute unit) 890, a last round of up to
+// 256 of those (one per unit) 620, a tail of halves 520 and 14 for each of an XCD's tiles
+// (at 16, 1024 x 4096 x 12288, the 128 x 128 tiles stay: per-channel 54.4 us, with the
+// tail 57). Measured: 2048 x K x 12288 (768 / 1536 tiles) 2.34 / 2.67 us per K tile,
+// 512 x 8192 x 8192 (128 / 256 tiles) 51.7 / 45 us in all.
+bool small_tiles(int M, int N, int K) {
   const long tn = (N + 127) / 128;
   const long t256 = (long)((M + 255) / 256) * tn, t128 = (long)((M + 127) / 128) * tn;
-  const long large = (t256 + 255) / 256 * 780;
+  const TailSplit sp = tail_split(M, N, K);
+  const long large = sp.tail ? (sp.per - sp.tail) / 32 * 780 + 520 + 14 * sp.tail
+                             : (t256 + 255) / 256 * 780;
   const long rest = t128 % 512;
   return t128 / 512 * 890 + (rest == 0 ? 0 : rest <= 256 ? 620 : 890) < large;
 }
@@ -646,7 +726,7 @@ hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const f
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const bool teams = split_teams(M, N, K);
-  const bool small = teams || small_tiles(M, N);
+  const bool small = teams || small_tiles(M, N, K);
 #define RRS_ARGS \
   Xe, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale, stream, border
 #define RRS_LAY(WMC_, KS_, PC_, GA_)                                       \

@@ -1,7 +1,7 @@
 """The many-token GEMM on scratch memory (6-bit operands) against the entry points
 without scratch (int8 operands): the partials of both are exact and each is
 added with one FMA in the same order, so Y must be the same bits. (Where two teams
-share a tile the order differs; the second test holds those to the binary64 sum,
+share a tile, or the halves of the last round's tiles, the order differs; the second test holds those to the binary64 sum,
 with the bound of the mid-size kernel's test.) Codes are all
 sixteen nibbles, at the edges of the tiles: ragged rows (a last block of 32 rows
 partly or wholly past M) and columns, both tile shapes, every group size (64 at K =
@@ -32,9 +32,9 @@ def _st():
 
 
 CASES = [  # 128 x 128 tiles, then 256 x 128
-    (500, 512, 6208, 128, False), (777, 1024, 4160, 64, True), (500, 16384, 17008, 64, False),
-    (500, 2048, 17008, 512, True),
-    (1030, 1024, 5200, 128, True), (1057, 512, 5136, 64, False), (1300, 2048, 6160, 256, False),
+    (500, 512, 6208, 128, False), (777, 1024, 4160, 64, True), (500, 16384, 12304, 64, False),
+    (500, 1024, 17008, 512, True),
+    (1030, 1024, 5200, 128, True), (1057, 512, 5136, 64, False), (1300, 1024, 6160, 256, False),
     (2049, 1024, 4624, 512, False),
 ]
 
@@ -78,6 +78,11 @@ def test_scratch_gemm_same_bits(M, K, N, g, tiled):
 # Two teams: from 513 tiles of 64 x 64 to 256 of 128 x 128, K from 2048.
 TEAMS = [(520, 2048, 4112, 128, False), (577, 2048, 3600, 64, True), (70, 2048, 16400, 512, True),
          (1000, 4096, 2064, 256, False), (1024, 2048, 4096, 128, True)]
+# The last tiles of 256 x 128 as halves with two teams: 294 and 266 tiles, 265 with a last
+# half past M, 384 (the most halves), 520 (two full rounds).
+TEAMS += [(1300, 2048, 6160, 256, False), (500, 2048, 17008, 512, True),
+          (1070, 2048, 6736, 128, True), (1024, 2048, 12288, 512, False),
+          (1250, 4096, 13312, 512, False)]
 
 
 @pytest.mark.parametrize("M,K,N,g,tiled", TEAMS)
