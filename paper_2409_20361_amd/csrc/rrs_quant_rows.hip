@@ -285,17 +285,18 @@ hipError_t launch_k(const uint16_t* X, int M, int g, bool rotate, uint8_t* Xq, f
 bool quant_rows_fits(int M) { return M >= 1 && M <= kMaxRows; }
 
 // Read ahead for the weight-streaming kernels (up to 16 tokens), as much as fits behind
-// the quantizer's own time, which grows with K: 8 MB at K = 2048 and 8 MB more per
+// the quantizer's own time, which grows with K: 16 MB at K = 4096 and 8 MB more per
 // doubling. Layer calls, weights cold (us; none, then 16 / 24 / 32 MB): K = 4096, N =
 // 12288, M = 3, 12.96, 12.04 / 12.07 / 12.06; K = 8192, N = 28672, M = 8, 28.9, 28.0 /
-// 27.6 / 27.7; K = 16384, N = 4096, M = 16, 23.6, 22.7 / 22.5 / 21.1; at K = 2048, N =
-// 22016, M = 16 16 MB are too much (15.5, 15.6 / 16.3). At K = 1024 the call is bound by
-// the host and nothing is gained (4 tokens, 10.7). The mid-size kernel, whose weights
-// other compute units read, gains nothing (49 x 4096 x 22016 23.2, 24.1 / 24.3 / 24.4).
+// 27.6 / 27.7; K = 16384, N = 4096, M = 16, 23.6, 22.7 / 22.5 / 21.1. Below, the quantizer
+// is too short: K = 2048, N = 22016, 16 tokens, 15.5, with 16 MB 15.6; three layers of 8
+// tokens whose weights the memory-side cache holds 38.7, with 8 MB 39.8. At K = 1024 the
+// call is bound by the host. The mid-size kernel, whose weights other compute units read,
+// gains nothing (49 x 4096 x 22016 23.2, 24.1 / 24.3 / 24.4).
 WeightAhead weight_ahead(const uint8_t* Wq, int M, int N, int K) {
-  if (!quant_rows_fits(M) || K < 2048) return {};
-  long mb = 8;
-  for (int k = 2048; k < K; k *= 2) mb += 8;
+  if (!quant_rows_fits(M) || K < 4096) return {};
+  long mb = 16;
+  for (int k = 4096; k < K; k *= 2) mb += 8;
   const long most = (mb << 20) / (8 * K);
   return {Wq, (int)(most < N / 16 ? most : N / 16)};
 }

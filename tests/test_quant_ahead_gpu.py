@@ -1,6 +1,6 @@
 """The layer calls of up to 16 tokens, whose quantizer launch also reads the first weights of
 the GEMM behind it: fewer column blocks than reading workgroups, one more than those, more than
-are read ahead (512 blocks at K = 2048), the largest K, a K below the rule. The outputs are the
+are read ahead (512 blocks at K = 4096), the largest K, Ks below the rule. The outputs are the
 bits of the separate quantizer and GEMM calls (which read nothing ahead), also over consecutive
 calls on one workspace, and the rows' exchange reports no failed wait."""
 import pytest
@@ -12,8 +12,8 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("reorder", [False, True])
 @pytest.mark.parametrize("tiled", [False, True])
-@pytest.mark.parametrize("M,K,N,g", [(3, 2048, 16, 64), (16, 2048, 16 * 161, 128),
-                                     (5, 2048, 16 * 600, 512), (16, 4096, 16 * 77, 128),
+@pytest.mark.parametrize("M,K,N,g", [(3, 4096, 16, 64), (16, 4096, 16 * 161, 128),
+                                     (5, 4096, 16 * 600, 512), (16, 2048, 16 * 77, 128),
                                      (8, 8192, 16 * 9, 128), (16, 16384, 16 * 170, 64),
                                      (2, 16384, 48, 512), (4, 1024, 16 * 33, 128)])
 def test_layer_reading_ahead(M, K, N, g, tiled, reorder):
