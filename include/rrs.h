@@ -507,6 +507,14 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
  * used (few tokens, or invalid arguments). Any group size and flags. */
 size_t rrs_gemm_scratch_bytes(int M, int N, int K);
 
+/* Test hook: the name of the kernel a GEMM call takes, a host query ("stream",
+ * "stream_gather", "decode", "decode_gather", "mid", "main", "fp6_teams", "fp6_small",
+ * "fp6_large", "fp6_tail"; "" for invalid arguments). scheme:
+ * RRS_SCHEME_RUNTIME_SMOOTH or RRS_SCHEME_PER_CHANNEL (group_size then not read);
+ * reorder: with block_order; scratch: with rrs_gemm_scratch_bytes of scratch. */
+const char* rrs_test_gemm_path(int M, int N, int K, int group_size, int flags, int scheme,
+                               int reorder, int scratch);
+
 /* rrs_w4a4_gemm_ex; with block_order rrs_w4a4_gemm_reorder; with s_group NULL
  * (then block_order too, and group_size ignored) rrs_w4a4_gemm_per_channel. */
 rrs_status rrs_w4a4_gemm_scratch(const void* Xq, const float* a_scale, const float* s_group,

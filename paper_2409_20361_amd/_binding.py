@@ -53,6 +53,7 @@ _SIGNATURES = {
                               [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp]),
     "rrs_linear_reorder": (ctypes.c_int32,
                            [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _sz, _vp]),
+    "rrs_test_gemm_path": (ctypes.c_char_p, [_i, _i, _i, _i, _i, _i, _i, _i]),
     "rrs_gemm_scratch_bytes": (_sz, [_i, _i, _i]),
     "rrs_w4a4_gemm_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i,
                                                _vp, _vp, _sz, _vp]),
@@ -276,6 +277,15 @@ def w4a4_gemm_partials(Xq: torch.Tensor, Wq: torch.Tensor, g: int) -> torch.Tens
     _check(lib().rrs_w4a4_gemm_partials(xp, wp, M, N, K, g, P.data_ptr(), _stream(Xq.device)),
            "rrs_w4a4_gemm_partials")
     return P
+
+
+def gemm_path(M: int, N: int, K: int, g: int, flags: int = 0, reorder: bool = False,
+              per_channel: bool = False, scratch: bool = True) -> str:
+    """Name of the kernel a GEMM call takes (test hook, a host query; include/rrs.h). The
+    calls of this module give the scratch that the shape asks for."""
+    return lib().rrs_test_gemm_path(
+        M, N, K, g, flags, SCHEME_PER_CHANNEL if per_channel else SCHEME_RUNTIME_SMOOTH,
+        int(reorder), int(scratch)).decode()
 
 
 def quant_rows_wait_hook(X: torch.Tensor, g: int, extra_rows: int, max_polls: int,

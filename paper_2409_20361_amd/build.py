@@ -18,8 +18,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librrs.so")
 OBJDIR = os.path.join(PKG, "_build")
 
-SOURCES = ["rrs_api.cpp", "rrs_quant.hip", "rrs_weight.hip", "rrs_gemm.hip", "rrs_gemm_small.hip",
-           "rrs_gemm_decode.hip", "rrs_quant_wave.hip", "rrs_reorder.hip", "rrs_quant_rows.hip",
+SOURCES = ["rrs_api.cpp", "rrs_gemm_route.cpp", "rrs_quant.hip", "rrs_weight.hip", "rrs_gemm.hip",
+           "rrs_gemm_small.hip", "rrs_gemm_decode.hip", "rrs_quant_wave.hip", "rrs_reorder.hip", "rrs_quant_rows.hip",
            "rrs_gemm_stream.hip", "rrs_gemm_stream_gather.hip", "rrs_gemm_mid.hip",
            "rrs_gemm_fp6.hip", "rrs_noalloc.hip"]
 

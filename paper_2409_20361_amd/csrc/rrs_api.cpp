@@ -428,12 +428,10 @@ hipError_t run_gemm(const void* Xq, const float* a, const float* s, const void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const float os = out_scale(K, flags);
   const rrs::WqLayout lay = layout(flags);
-  // Without the rescale the mid-size kernel stays ahead where it fits (300 x 8192 x
-  // 8192: 33 against 35.5 us).
-  if (scratch && (s || !rrs::mid_kernel_fits(M, N))) {
-    const size_t need = rrs::fp6_scratch_bytes(M, N, K);
-    if (need && scratch_bytes >= need)
-      return rrs::launch_w4a4_gemm_fp6(xq, a, s, wq, w, border, M, N, K, g, y, os, scratch, st,
+  if (scratch && scratch_bytes >= rrs::fp6_scratch_bytes(M, N, K)) {
+    const rrs::GemmPath p = rrs::gemm_path({M, N, K, g, !s, border != nullptr, lay.tiled}, true);
+    if (rrs::on_scratch(p))
+      return rrs::launch_w4a4_gemm_fp6(p, xq, a, s, wq, w, border, M, N, K, g, y, os, scratch, st,
                                        lay);
   }
   if (!s) return rrs::launch_w4a4_gemm_per_channel(xq, a, wq, w, M, N, K, y, os, st, lay);
@@ -449,6 +447,16 @@ extern "C" {
 size_t rrs_gemm_scratch_bytes(int M, int N, int K) {
   if (!valid_m(M) || !valid_n(N) || !valid_k(K)) return 0;
   return rrs::fp6_scratch_bytes(M, N, K);
+}
+
+const char* rrs_test_gemm_path(int M, int N, int K, int group_size, int flags, int scheme,
+                               int reorder, int scratch) {
+  const bool per_channel = scheme == RRS_SCHEME_PER_CHANNEL;
+  if (!valid_m(M) || !valid_n(N) || !valid_k(K) || (per_channel && reorder) ||
+      (!per_channel && !valid_group(K, group_size)))
+    return "";
+  return rrs::gemm_path_name(rrs::gemm_path(
+      {M, N, K, group_size, per_channel, reorder != 0, layout(flags).tiled}, scratch != 0));
 }
 
 rrs_status rrs_w4a4_gemm_ex(const void* Xq, const float* a_scale, const float* s_group,

@@ -440,7 +440,8 @@ hipError_t launch_main(const uint8_t* Xq, const float* a_scale, const float* s_g
   return hipGetLastError();
 }
 
-// The main kernel unrolls max(8, g / 32) k-steps per loop trip.
+// The main kernel unrolls max(8, g / 32) k-steps per loop trip, which divide
+// every K the ABI accepts (K / 32 >= 16 is a power of two).
 bool main_kernel_fits(int K, int g) {
   const int U = (g / 32 > 8) ? g / 32 : 8;
   return (K / 32) % U == 0;
@@ -452,15 +453,18 @@ hipError_t launch_w4a4_gemm(const uint8_t* Xq, const float* a_scale, const float
                             const uint8_t* Wq, const float* w_scale, int M, int N, int K,
                             int g, uint16_t* Y, float out_scale, hipStream_t stream,
                             WqLayout lay) {
-  if (stream_kernel_fits(M, K, g))
-    return launch_w4a4_gemm_stream(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
-                                   stream, lay);
-  if (decode_kernel_fits(M))
-    return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
-                                   stream, nullptr, lay);
-  if (mid_kernel_fits(M, N))
-    return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, nullptr, M, N, K, g, Y,
-                                out_scale, stream, lay);
+  switch (gemm_path({M, N, K, g, false, false, lay.tiled}, false)) {
+    case GemmPath::kStream:
+      return launch_w4a4_gemm_stream(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
+                                     stream, lay);
+    case GemmPath::kDecode:
+      return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
+                                     stream, nullptr, lay);
+    case GemmPath::kMid:
+      return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, nullptr, M, N, K, g, Y,
+                                  out_scale, stream, lay);
+    default: break;
+  }
   if (!main_kernel_fits(K, g))
     return launch_w4a4_gemm_small(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
                                   stream, lay);
@@ -472,9 +476,7 @@ hipError_t launch_w4a4_gemm_per_channel(const uint8_t* Xq, const float* a_scale,
                                        const uint8_t* Wq, const float* w_scale, int M, int N,
                                        int K, uint16_t* Y, float out_scale, hipStream_t stream,
                                        WqLayout lay) {
-  // Up to 16 tokens too: this scheme has no few-token kernel of its own, and the
-  // main kernel's 256-row tiles took 35 us at K = N = 4096 whatever M is.
-  if (M <= 16 || mid_kernel_fits(M, N))
+  if (gemm_path({M, N, K, 0, true, false, lay.tiled}, false) == GemmPath::kMid)
     return launch_w4a4_gemm_mid_per_channel(Xq, a_scale, Wq, w_scale, M, N, K, Y, out_scale,
                                             stream, lay);
   if (!main_kernel_fits(K, 128))
@@ -497,15 +499,18 @@ hipError_t launch_w4a4_gemm_reorder(const uint8_t* Xq, const float* a_scale,
                                     const float* w_scale, const int32_t* border, int M, int N,
                                     int K, int g, uint16_t* Y, float out_scale,
                                     hipStream_t stream, WqLayout lay) {
-  if (stream_gather_fits(M, K))
-    return launch_w4a4_gemm_stream_gather(Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g,
-                                          Y, out_scale, stream, lay);
-  if (decode_gather_fits(M))
-    return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
-                                   stream, border, lay);
-  if (mid_kernel_fits(M, N))
-    return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g, Y,
-                                out_scale, stream, lay);
+  switch (gemm_path({M, N, K, g, false, true, lay.tiled}, false)) {
+    case GemmPath::kStreamGather:
+      return launch_w4a4_gemm_stream_gather(Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g,
+                                            Y, out_scale, stream, lay);
+    case GemmPath::kDecodeGather:
+      return launch_w4a4_gemm_decode(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale,
+                                     stream, border, lay);
+    case GemmPath::kMid:
+      return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g, Y,
+                                  out_scale, stream, lay);
+    default: break;
+  }
   // Every shape the ABI accepts fits the main kernel (K / 32 >= 16 is a power
   // of two); the fallback kernel has no gather.
   if (!main_kernel_fits(K, g)) return hipErrorInvalidValue;
@@ -516,12 +521,14 @@ hipError_t launch_w4a4_gemm_reorder(const uint8_t* Xq, const float* a_scale,
 hipError_t launch_w4a4_gemm_partials(const uint8_t* Xq, const uint8_t* Wq, int M, int N,
                                      int K, int g, int32_t* P, hipStream_t stream,
                                      WqLayout lay) {
-  // The kernel rrs_w4a4_gemm would take for this shape (row-major Wq).
-  if (stream_kernel_fits(M, K, g))
+  // The kernel rrs_w4a4_gemm takes for this shape; the hooks of the few-token and
+  // mid-size kernels read a row-major Wq.
+  const GemmPath p = gemm_path({M, N, K, g, false, false, lay.tiled}, false);
+  if (p == GemmPath::kStream)
     return launch_w4a4_gemm_stream_partials(Xq, Wq, M, N, K, g, P, stream, lay);
-  if (decode_kernel_fits(M) && !lay.tiled)
+  if (p == GemmPath::kDecode && !lay.tiled)
     return launch_w4a4_gemm_decode_partials(Xq, Wq, M, N, K, g, P, stream);
-  if (mid_kernel_fits(M, N) && !lay.tiled)
+  if (p == GemmPath::kMid && !lay.tiled)
     return launch_w4a4_gemm_mid_partials(Xq, Wq, M, N, K, g, P, stream);
   if (!main_kernel_fits(K, g))
     return launch_w4a4_gemm_partials_small(Xq, Wq, M, N, K, g, P, stream, lay);

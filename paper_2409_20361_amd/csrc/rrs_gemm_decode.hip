@@ -1,5 +1,5 @@
-// W4A4 GEMM with Runtime Smooth for few tokens (decode: M <= 16), the same
-// product as the main kernel (Section 3.2, Eq. 3, Fig. 4 step (3)):
+// W4A4 GEMM with Runtime Smooth for few tokens (decode: M <= 16, some forms up to
+// 64), the same product as the main kernel (Section 3.2, Eq. 3, Fig. 4 step (3)):
 //   Y[i, n] = fp16( alpha_i * beta_n / K * sum_b s_b * P_b[i, n] )
 //   P_b[i, n] = sum_{j in group b} qx[i, j] * qw[j, n]   (exact int32)
 //
@@ -7,12 +7,17 @@
 // the chip once; the matrix core only has to keep up. The kernel therefore
 // maximizes the weight bytes in flight and never stages them in LDS:
 //   - a workgroup owns two blocks of 16 output columns (rows of Wq; four
-//     blocks with row-major weights from 8 tokens on); its four
+//     blocks with row-major weights from 8 tokens on and with either layout
+//     above 16 tokens); its four
 //     waves take every fourth smoothing group (wave w: groups w, w + 4, ...,
 //     so the four read neighbouring groups of the same rows together) and
 //     add their fp32 partial sums in a fixed order at the end
 //     (deterministic); each wave unpacks its token codes once for both
 //     blocks;
+//   - tokens come in up to four blocks of 16 (TB), every block multiplied
+//     with the same weight words, so the weights still stream once for up to
+//     64 tokens (the 256-row tiles of the main kernel would leave most of
+//     their MFMA work idle at such M);
 //   - per group, lane (c, q) (c = lane % 16, q = lane / 16) takes g/8 bytes
 //     of Wq row n0 + c and the same bytes of Xq row c (zero for c >= M): for
 //     g = 64 bytes [8 q, 8 q + 8) of the group, for g >= 128 bytes
@@ -42,8 +47,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;  // 4 waves: K quarters of the same columns
 constexpr int kCols = 16;      // columns per MFMA block
-constexpr int kBlocks = 2;     // column blocks per workgroup (they share the A unpack); or four
-                               // (launcher)
+constexpr int kBlocks = 2;     // column blocks per workgroup (they share the A unpack); four
+                               // for larger token counts (launcher)
 
 __device__ __forceinline__ v4i unpack_pair(uint32_t w0, uint32_t w1) {
   v4i r;
@@ -78,11 +83,13 @@ __device__ __forceinline__ void load_words(const uint8_t* __restrict__ p, int st
 // Groups per wave: a quarter of the groups (one each when K has fewer than
 // four groups; waves past the last group get none).
 __host__ __device__ inline int groups_per_wave(int K, int g) { return K / g >= 4 ? K / g / 4 : 1; }
+constexpr int kMaxTokenBlocks = 4;  // up to 64 tokens
 
-// GS = g / 64 MFMA k-steps per group, KB column blocks per workgroup.
+// GS = g / 64 MFMA k-steps per group; TB token blocks of 16 rows (tokens
+// 16 tb .. 16 tb + 15 in block tb), all multiplied with the same weight words.
 // kPartials (test hook): instead of Y, write P[b][i][n] for every group b,
 // token i < M and column n, decoded from the same seeded accumulators.
-template <int GS, bool kTiled, int KB, bool kPartials = false>
+template <int GS, int TB, bool kTiled, int KB, bool kPartials = false>
 __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
     const uint8_t* __restrict__ Xq, const float* __restrict__ a_scale,
     const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
@@ -91,10 +98,11 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
   constexpr WqLayout lay{kTiled};
   constexpr int g = GS * 64;
   constexpr int NW = g / 32;                  // words per lane per group and block
-  constexpr int D = NW >= 16 ? 1 : (NW >= 8 ? 2 : 4);  // groups in flight
+  constexpr int D0 = NW >= 16 ? 1 : (NW >= 8 ? 2 : 4);
+  constexpr int D = TB >= 4 && D0 > 1 ? D0 / 2 : D0;  // groups in flight
   // The four waves' fp32 partial sums, added at the end.
-  __shared__ __attribute__((aligned(16))) uint8_t lds[4 * KB * 64 * 16];
-  v4f(*part)[KB][64] = reinterpret_cast<v4f(*)[KB][64]>(lds);
+  __shared__ __attribute__((aligned(16))) uint8_t lds[4 * TB * KB * 64 * 16];
+  v4f(*part)[TB][KB][64] = reinterpret_cast<v4f(*)[TB][KB][64]>(lds);
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -126,7 +134,9 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
   constexpr int wts = lay.tile();
   const int wo = g == 64 ? (q >> 1) * wqs + (q & 1) * 8 : q * wqs;
   constexpr size_t gstride = kTiled ? (size_t)8 * g : (size_t)(g / 2);
-  const uint8_t* pa = Xq + (size_t)min(c, M - 1) * krow + xo;
+  const uint8_t* pa[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) pa[tb] = Xq + (size_t)min(16 * tb + c, M - 1) * krow + xo;
   const uint8_t* pb[KB];
 #pragma unroll
   for (int j = 0; j < KB; ++j) {
@@ -134,63 +144,75 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
     pb[j] = Wq + lay.row(n + c, K) + wo;
   }
 
-  uint32_t wa[D][NW], wb[D][KB][NW];
+  uint32_t wa[D][TB][NW], wb[D][KB][NW];
   auto load = [&](int d, int i) {
     const int b = min(kq + 4 * i, G - 1);
-    load_words<NW>(pa + (size_t)b * (g / 2), 64, wa[d]);
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) load_words<NW>(pa[tb] + (size_t)b * (g / 2), 64, wa[d][tb]);
 #pragma unroll
     for (int j = 0; j < KB; ++j) load_words<NW>(pb[j] + (size_t)b * gstride, wts, wb[d][j]);
   };
 
   constexpr int kMagic = 0x4B400000;  // bits of 1.5 * 2^23
   const v4i seed = GS > 4 ? v4i{0, 0, 0, 0} : v4i{kMagic, kMagic, kMagic, kMagic};
-  float f[KB][4];
+  float f[TB][KB][4];
 #pragma unroll
-  for (int j = 0; j < KB; ++j)
+  for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) f[j][r] = 0.0f;
+    for (int j = 0; j < KB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f[tb][j][r] = 0.0f;
 
   auto consume = [&](int d, int i) {
     const float s = (!kPartials && i < nb) ? s_group[min(kq + 4 * i, G - 1)] : 0.0f;
-    v4i acc[KB];
+    v4i acc[TB][KB];
 #pragma unroll
-    for (int j = 0; j < KB; ++j) acc[j] = seed;
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+      for (int j = 0; j < KB; ++j) acc[tb][j] = seed;
 #pragma unroll
     for (int st = 0; st < GS; ++st) {
       v4i bv[KB];
 #pragma unroll
       for (int j = 0; j < KB; ++j) bv[j] = unpack_pair(wb[d][j][2 * st], wb[d][j][2 * st + 1]);
-      const v4i a = unpack_pair(wa[d][2 * st], wa[d][2 * st + 1]);
 #pragma unroll
-      for (int j = 0; j < KB; ++j)
-        acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv[j], acc[j], 0, 0, 0);
+      for (int tb = 0; tb < TB; ++tb) {
+        const v4i a = unpack_pair(wa[d][tb][2 * st], wa[d][tb][2 * st + 1]);
+#pragma unroll
+        for (int j = 0; j < KB; ++j)
+          acc[tb][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv[j], acc[tb][j], 0, 0, 0);
+      }
     }
     if constexpr (kPartials) {
       if (i < nb) {
         int32_t* Pg = P + (size_t)(kq + 4 * i) * (size_t)M * (size_t)N;
 #pragma unroll
-        for (int j = 0; j < KB; ++j)
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = 4 * q + r;
-            const int col = n0 + j * kCols + c;
-            const int v = acc[j][r];
-            if (row < M && col < N) Pg[(size_t)row * N + col] = (GS > 4 ? v : v - kMagic) >> 8;
-          }
+          for (int j = 0; j < KB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int row = 16 * tb + 4 * q + r;
+              const int col = n0 + j * kCols + c;
+              const int v = acc[tb][j][r];
+              if (row < M && col < N) Pg[(size_t)row * N + col] = (GS > 4 ? v : v - kMagic) >> 8;
+            }
       }
       return;
     }
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      // Bit-cast the whole vector, then index: bit-casting a single element
-      // of an ext_vector is miscompiled (every element reads element 0).
-      const v4f accf = __builtin_bit_cast(v4f, acc[j]);
+    for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float pv = GS > 4 ? (float)acc[j][r] : accf[r] - 12582912.0f;
-        f[j][r] = __builtin_fmaf(s, pv, f[j][r]);
+      for (int j = 0; j < KB; ++j) {
+        // Bit-cast the whole vector, then index: bit-casting a single element
+        // of an ext_vector is miscompiled (every element reads element 0).
+        const v4f accf = __builtin_bit_cast(v4f, acc[tb][j]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float pv = GS > 4 ? (float)acc[tb][j][r] : accf[r] - 12582912.0f;
+          f[tb][j][r] = __builtin_fmaf(s, pv, f[tb][j][r]);
+        }
       }
-    }
   };
 
 #pragma unroll
@@ -209,7 +231,10 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
   if constexpr (kPartials) return;
   // Partial sums of the four K quarters, added in a fixed order.
 #pragma unroll
-  for (int j = 0; j < KB; ++j) part[kq][j][lane] = v4f{f[j][0], f[j][1], f[j][2], f[j][3]};
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int j = 0; j < KB; ++j)
+      part[kq][tb][j][lane] = v4f{f[tb][j][0], f[tb][j][1], f[tb][j][2], f[tb][j][3]};
   __syncthreads();
   // Wave w stores column block w (if any): sums in the order kq = 0, 1, 2, 3.
   const int w = t >> 6;
@@ -219,22 +244,26 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_kernel(
     const float inv = out_scale;
     const int col = n0 + w * kCols + c;
     const float bcol = w_scale[col];
-    v4f sum = part[0][w][lane];
 #pragma unroll
-    for (int p = 1; p < 4; ++p) {
-      const v4f x = part[p][w][lane];
-      sum.x += x.x;
-      sum.y += x.y;
-      sum.z += x.z;
-      sum.w += x.w;
-    }
-    const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
+    for (int tb = 0; tb < TB; ++tb) {
+      v4f sum = part[0][tb][w][lane];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 4 * q + r;  // output row of accumulator r of this lane
-      if (row < M) {
-        const float sc = a_scale[row] * inv;
-        Y[(size_t)row * N + col] = __builtin_bit_cast(uint16_t, (_Float16)((sv[r] * sc) * bcol));
+      for (int p = 1; p < 4; ++p) {
+        const v4f x = part[p][tb][w][lane];
+        sum.x += x.x;
+        sum.y += x.y;
+        sum.z += x.z;
+        sum.w += x.w;
+      }
+      const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * tb + 4 * q + r;  // output row of accumulator r of this lane
+        if (row < M) {
+          const float sc = a_scale[row] * inv;
+          Y[(size_t)row * N + col] =
+              __builtin_bit_cast(uint16_t, (_Float16)((sv[r] * sc) * bcol));
+        }
       }
     }
   }
@@ -428,46 +457,83 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_gather_kernel(
 
 }  // namespace
 
-bool decode_kernel_fits(int M) { return M >= 1 && M <= kCols; }
+// Above 16 tokens, the forms the route takes (rrs_gemm_route.cpp): long groups, or
+// two groups of 64 per wave (K = 512).
+bool decode_wide_fits(int M, int K, int g, bool tiled) {
+  if (M <= kCols || M > kCols * kMaxTokenBlocks) return false;
+  if (M > 2 * kCols) return (g >= 256 && !tiled) || (g == 64 && K == 512);
+  return g >= 256 && (g == 512 || !tiled);
+}
+
+namespace {
+
+// Four column blocks per workgroup (64 rows of Wq) for row-major weights
+// from 8 tokens on and for either layout above 16 tokens (at the decode
+// shape, row-major: 3 % faster at M = 8, 19 % at M = 64).
+template <int GS, int TB, bool kTiled, int KB, bool kPartials>
+hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                  const uint8_t* Wq, const float* w_scale, int M, int N, int K, uint16_t* Y,
+                  float out_scale, int32_t* P, hipStream_t stream) {
+  const int grid = (N / kCols + KB - 1) / KB;  // N % 16 == 0 (API precondition)
+  gemm_decode_kernel<GS, TB, kTiled, KB, kPartials><<<grid, kThreads, 0, stream>>>(
+      Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, out_scale, P);
+  return hipGetLastError();
+}
+
+template <int GS, bool kTiled, bool kPartials>
+hipError_t launch_gs(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                     const uint8_t* Wq, const float* w_scale, int M, int N, int K, uint16_t* Y,
+                     float out_scale, int32_t* P, hipStream_t stream) {
+#define RRS_DECODE(TB_, KB_)                                                               \
+  return launch<GS, TB_, kTiled, KB_, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, \
+                                                 out_scale, P, stream)
+  if (M <= kCols) {
+    if constexpr (!kTiled)
+      if (M >= 8) RRS_DECODE(1, 4);
+    RRS_DECODE(1, kBlocks);
+  }
+  if (!decode_wide_fits(M, K, GS * 64, kTiled)) return hipErrorInvalidValue;
+  if constexpr (GS == 8 || (GS == 4 && !kTiled))
+    if (M <= 2 * kCols) RRS_DECODE(2, 4);
+  if constexpr (GS == 1 || (GS >= 4 && !kTiled)) RRS_DECODE(4, 4);
+  return hipErrorInvalidValue;
+#undef RRS_DECODE
+}
+
+template <bool kTiled, bool kPartials>
+hipError_t launch_g(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                    const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
+                    uint16_t* Y, float out_scale, int32_t* P, hipStream_t stream) {
+#define RRS_CASE(G_)                                                                           \
+  case G_:                                                                                     \
+    return launch_gs<G_ / 64, kTiled, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, \
+                                                 out_scale, P, stream)
+  switch (g) {
+    RRS_CASE(64);
+    RRS_CASE(128);
+    RRS_CASE(256);
+    RRS_CASE(512);
+    default: return hipErrorInvalidValue;
+  }
+#undef RRS_CASE
+}
+
+}  // namespace
 
 hipError_t launch_w4a4_gemm_decode_partials(const uint8_t* Xq, const uint8_t* Wq, int M, int N,
                                             int K, int g, int32_t* P, hipStream_t stream) {
-  // The same block choice as the row-major Y launch below.
-  const int grid = (N / kCols + kBlocks - 1) / kBlocks;
-  const int grid4 = (N / kCols + 3) / 4;
-  const bool kb4 = M >= 8;
-#define RRS_DECODE_P(GS_)                                                                   \
-  if (kb4)                                                                                 \
-    gemm_decode_kernel<GS_, false, 4, true><<<grid4, kThreads, 0, stream>>>(                 \
-        Xq, nullptr, nullptr, Wq, nullptr, M, N, K, nullptr, 0.0f, P);                      \
-  else                                                                                     \
-    gemm_decode_kernel<GS_, false, kBlocks, true><<<grid, kThreads, 0, stream>>>(           \
-        Xq, nullptr, nullptr, Wq, nullptr, M, N, K, nullptr, 0.0f, P);                      \
-  break
-  switch (g) {
-    case 64: RRS_DECODE_P(1);
-    case 128: RRS_DECODE_P(2);
-    case 256: RRS_DECODE_P(4);
-    case 512: RRS_DECODE_P(8);
-    default: return hipErrorInvalidValue;
-  }
-#undef RRS_DECODE_P
-  return hipGetLastError();
+  return launch_g<false, true>(Xq, nullptr, nullptr, Wq, nullptr, M, N, K, g, nullptr, 0.0f, P,
+                               stream);
 }
-bool decode_gather_fits(int M) { return M >= 1 && M <= kCols; }
 
 hipError_t launch_w4a4_gemm_decode(const uint8_t* Xq, const float* a_scale,
                                    const float* s_group, const uint8_t* Wq,
                                    const float* w_scale, int M, int N, int K, int g,
                                    uint16_t* Y, float out_scale, hipStream_t stream,
                                    const int32_t* border, WqLayout lay) {
-  const int grid = (N / kCols + kBlocks - 1) / kBlocks;  // N % 16 == 0 (API precondition)
-  // Four column blocks per workgroup (64 rows of Wq) for row-major weights
-  // from 8 tokens on (3 % faster at the decode shape).
-  const bool kb4 = !lay.tiled && M >= 8;
-  const int grid4 = (N / kCols + 3) / 4;
-  if (M > kCols) return hipErrorInvalidValue;  // one block of tokens
   if (border) {
+    if (M > kCols) return hipErrorInvalidValue;  // the gather kernel takes one token block
+    const int grid = (N / kCols + kBlocks - 1) / kBlocks;
     if (lay.tiled)
       gemm_decode_gather_kernel<true><<<grid, kThreads, 0, stream>>>(
           Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g, Y, out_scale);
@@ -476,26 +542,10 @@ hipError_t launch_w4a4_gemm_decode(const uint8_t* Xq, const float* a_scale,
           Xq, a_scale, s_group, Wq, w_scale, border, M, N, K, g, Y, out_scale);
     return hipGetLastError();
   }
-#define RRS_DECODE(GS_)                                                    \
-  if (lay.tiled)                                                          \
-    gemm_decode_kernel<GS_, true, kBlocks><<<grid, kThreads, 0, stream>>>(  \
-        Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, out_scale);        \
-  else if (kb4)                                                           \
-    gemm_decode_kernel<GS_, false, 4><<<grid4, kThreads, 0, stream>>>(      \
-        Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, out_scale);        \
-  else                                                                    \
-    gemm_decode_kernel<GS_, false, kBlocks><<<grid, kThreads, 0, stream>>>( \
-        Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, out_scale);        \
-  break
-  switch (g) {
-    case 64: RRS_DECODE(1);
-    case 128: RRS_DECODE(2);
-    case 256: RRS_DECODE(4);
-    case 512: RRS_DECODE(8);
-    default: return hipErrorInvalidValue;
-  }
-#undef RRS_DECODE
-  return hipGetLastError();
+  return lay.tiled ? launch_g<true, false>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y,
+                                           out_scale, nullptr, stream)
+                   : launch_g<false, false>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y,
+                                            out_scale, nullptr, stream);
 }
 
 }  // namespace rrs

@@ -634,13 +634,13 @@ TailSplit tail_split(int M, int N, int K) {
 }
 
 template <int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
-hipError_t launch_gemm(const uint8_t* Xe, const float* a_scale, const float* s_group,
+hipError_t launch_gemm(bool tail, const uint8_t* Xe, const float* a_scale, const float* s_group,
                        const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
                        uint16_t* Y, float out_scale, hipStream_t stream, const int32_t* border) {
   using S = Shape<WMC>;
   const int T = ((M + S::BM - 1) / S::BM) * ((N + S::BN - 1) / S::BN);
   const int grid = 8 * ((T + 7) / 8);
-  const TailSplit sp = WMC == 4 ? tail_split(M, N, K) : TailSplit{0, 0};
+  const TailSplit sp = tail ? tail_split(M, N, K) : TailSplit{0, 0};
   const int full = 8 * (sp.per - sp.tail);
 #define RRS_FP6(G_)                                                                        \
   case G_:                                                                                 \
@@ -716,7 +716,13 @@ size_t fp6_scratch_bytes(int M, int N, int K) {
   return n <= ((size_t)1 << 30) ? n : 0;
 }
 
-hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const float* s_group,
+GemmPath fp6_form(int M, int N, int K) {
+  if (split_teams(M, N, K)) return GemmPath::kFp6Teams;
+  if (small_tiles(M, N, K)) return GemmPath::kFp6Small;
+  return tail_split(M, N, K).tail ? GemmPath::kFp6Tail : GemmPath::kFp6Large;
+}
+
+hipError_t launch_w4a4_gemm_fp6(GemmPath path, const uint8_t* Xq, const float* a_scale, const float* s_group,
                                 const uint8_t* Wq, const float* w_scale, const int32_t* border,
                                 int M, int N, int K, int g, uint16_t* Y, float out_scale,
                                 void* scratch, hipStream_t stream, WqLayout lay) {
@@ -725,10 +731,10 @@ hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const f
   expand_tokens_kernel<<<groups, 256, 0, stream>>>(Xq, M, K, Xe);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool teams = split_teams(M, N, K);
-  const bool small = teams || small_tiles(M, N, K);
+  const bool teams = path == GemmPath::kFp6Teams, small = path == GemmPath::kFp6Small;
+  const bool tail = path == GemmPath::kFp6Tail;
 #define RRS_ARGS \
-  Xe, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale, stream, border
+  tail, Xe, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, out_scale, stream, border
 #define RRS_LAY(WMC_, KS_, PC_, GA_)                                       \
   (lay.tiled ? launch_gemm<WMC_, KS_, PC_, GA_, true>(RRS_ARGS)            \
              : launch_gemm<WMC_, KS_, PC_, GA_, false>(RRS_ARGS))

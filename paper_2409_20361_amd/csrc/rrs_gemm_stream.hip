@@ -60,6 +60,16 @@
 //
 // Needs K >= 4 g (every wave holds whole groups): K = 512 with g <= 128,
 // K = 1024 with g <= 256, any g from K = 2048 (but g >= 256 at K = 16384).
+//
+// 17 to 32 tokens at K = 8192: the same loop with eight waves, each streaming
+// an eighth of K (16 rows x 512 bytes per block, the same 16 KB ring per wave)
+// and holding the codes of two blocks of 16 tokens (64 registers per block,
+// half of what a quarter of K would take), one workgroup of 512 threads per
+// compute unit (128 KB of ring and 32 KB of partial sums), each workgroup
+// streaming one contiguous range of column blocks. Every weight fragment is
+// unpacked once for both token blocks; the 2 x 4 (token block, accumulator
+// row) pairs of each lane are dealt to the eight waves for the fixed-order sum
+// and the stores.
 #include "rrs_device.h"
 #include "rrs_stream.h"
 
@@ -68,7 +78,9 @@ namespace {
 
 using namespace stream;
 
-// kPartials (test hook): instead of Y, write P[b][i][n] for
+// W waves per workgroup, each streaming a 1/W slice of K; TB blocks of 16
+// tokens (tokens 16 u .. 16 u + 15 in block u), all multiplied with the same
+// weight operands. kPartials (test hook): instead of Y, write P[b][i][n] for
 // every group b, token i < M and column n, decoded from the same seeded
 // accumulators.
 //
@@ -81,13 +93,13 @@ using namespace stream;
 // ring is laid out slot by slot), which no load touches before the loop,
 // while the first RS - 1 sub-buffers of weights stream in. (Xq, a_scale and
 // s_group are intermediates of the layer and are not written.)
-template <int K, int GS, bool kTiled, bool kPartials, int MQ = 0>
-__global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
+template <int K, int GS, int W, int TB, bool kTiled, bool kPartials, int MQ = 0>
+__global__ __launch_bounds__(64 * W) void gemm_stream_kernel(
     const uint8_t* __restrict__ Xq, const float* __restrict__ a_scale,
     const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
     const float* __restrict__ w_scale, int M, int N, uint16_t* __restrict__ Y,
     int32_t* __restrict__ P, float out_scale, const uint16_t* __restrict__ X) {
-  using S = StreamShape<K>;
+  using S = StreamShape<K, W>;
   constexpr int g = GS * 64;
   constexpr int GB = g / 2;                   // packed bytes of a row per group
   constexpr int NG = S::R / GB;               // groups per wave (its slice of K)
@@ -98,18 +110,18 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
   // The waves' fp32 sums of a block meet in `part`: double-buffered (one
   // barrier per block) when both copies fit beside the ring, else one copy
   // and a second barrier.
-  constexpr int kRingBytes = kWaves * S::RS * S::SB;
-  constexpr int kPartBytes = kWaves * 64 * 16;
+  constexpr int kRingBytes = W * S::RS * S::SB;
+  constexpr int kPartBytes = W * TB * 64 * 16;
   constexpr int PB = kRingBytes + 2 * kPartBytes <= 163840 ? 2 : 1;
   static_assert(kRingBytes + PB * kPartBytes <= 163840, "LDS of one workgroup");
   struct alignas(16) Lds {
     uint8_t ring[kRingBytes];
-    v4f part[PB][kWaves][64];  // follows the ring directly (kRingBytes % 16 == 0)
+    v4f part[PB][W][TB][64];  // follows the ring directly (kRingBytes % 16 == 0)
   };
   __shared__ Lds L;
   uint8_t* const ring = L.ring;
   auto& part = L.part;
-  static_assert(MQ == 0 || !kPartials, "one-launch layer: M <= 2");
+  static_assert(MQ == 0 || (W == 4 && TB == 1 && !kPartials), "one-launch layer: M <= 2");
   constexpr int G = K / g;
   __shared__ float qsg[MQ > 0 ? G : 1];  // s_b (one-launch layer)
   __shared__ float qred[MQ > 0 ? 4 * MQ : 1];
@@ -125,16 +137,20 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
   uint8_t* my = ring + kq * S::RS * S::SB;
   auto slot_of = [&](int i) -> uint8_t* {
     if constexpr (MQ > 0)
-      return ring + (i % S::RS) * (kWaves * S::SB) + kq * S::SB;
+      return ring + (i % S::RS) * (W * S::SB) + kq * S::SB;
     else
       return my + (i % S::RS) * S::SB;
   };
   const int nblk = N / kRows;
-  // Column blocks of this workgroup: w, w + grid, ... (one contiguous range
-  // streams 1.5 us slower at the decode shape, back-to-back calls).
-  const int b_lo = (int)blockIdx.x;
-  const int b_step = (int)gridDim.x;
-  const int mine = (nblk - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  // Column blocks of this workgroup: w, w + grid, ... with four waves (two
+  // workgroups per compute unit); one contiguous range with eight (one per
+  // compute unit), which streams 1-2 us faster there and 1.5 us slower with
+  // four (decode shape, back-to-back calls).
+  constexpr bool kRange = W == 8;
+  const int b_lo = kRange ? (int)(((long long)blockIdx.x * nblk) / (int)gridDim.x) : (int)blockIdx.x;
+  const int b_step = kRange ? 1 : (int)gridDim.x;
+  const int mine = kRange ? (int)(((long long)(blockIdx.x + 1) * nblk) / (int)gridDim.x) - b_lo
+                          : (nblk - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
   const int items = mine * S::SPB;  // sub-buffers this wave streams, in order
 
   // Direct loads of item i (sub-buffer i % SPB of column block i / SPB) into
@@ -196,10 +212,10 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
   if constexpr (MQ > 0) {
     constexpr int E = FwhtShape<K>::E;  // positions per thread (256 threads)
     static_assert(E >= 8 && E <= 64, "packed 8 codes at a time");
-    static_assert((kWaves * S::SB + PB * kPartBytes) >= lds_row_floats(K) * 4 &&
-                      (kWaves * S::SB + PB * kPartBytes) >= MQ * K / 2,
+    static_assert((W * S::SB + PB * kPartBytes) >= lds_row_floats(K) * 4 &&
+                      (W * S::SB + PB * kPartBytes) >= MQ * K / 2,
                   "scratch in the last ring slot and the partial sums");
-    float* scr = reinterpret_cast<float*>(ring + (S::RS - 1) * (kWaves * S::SB));
+    float* scr = reinterpret_cast<float*>(ring + (S::RS - 1) * (W * S::SB));
     float v[MQ][E];
 #pragma unroll
     for (int r = 0; r < MQ; ++r) {
@@ -262,26 +278,27 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
 
   // Token codes of the wave's slice (once per workgroup) and its group
   // scales (one per lane).
-  uint32_t aw[NG][NP][4];
-  {
-    const uint8_t* abase = tok + (size_t)min(c, M - 1) * krow + (size_t)kq * S::R;
+  uint32_t aw[TB][NG][NP][4];
+#pragma unroll
+  for (int u = 0; u < TB; ++u) {
+    const uint8_t* abase = tok + (size_t)min(16 * u + c, M - 1) * krow + (size_t)kq * S::R;
 #pragma unroll
     for (int b = 0; b < NG; ++b) {
       if constexpr (GB >= 64) {
 #pragma unroll
         for (int h = 0; h < NP; ++h) {
           const uint4 v = *reinterpret_cast<const uint4*>(abase + b * GB + 64 * h + 16 * q);
-          aw[b][h][0] = v.x;
-          aw[b][h][1] = v.y;
-          aw[b][h][2] = v.z;
-          aw[b][h][3] = v.w;
+          aw[u][b][h][0] = v.x;
+          aw[u][b][h][1] = v.y;
+          aw[u][b][h][2] = v.z;
+          aw[u][b][h][3] = v.w;
         }
       } else {
         const uint2 v = *reinterpret_cast<const uint2*>(abase + b * GB + 8 * q);
-        aw[b][0][0] = v.x;
-        aw[b][0][1] = v.y;
-        aw[b][0][2] = 0u;
-        aw[b][0][3] = 0u;
+        aw[u][b][0][0] = v.x;
+        aw[u][b][0][1] = v.y;
+        aw[u][b][0][2] = 0u;
+        aw[u][b][0][3] = 0u;
       }
     }
   }
@@ -294,14 +311,22 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
   constexpr int kMagic = 0x4B400000;  // bits of 1.5 * 2^23
   const v4i seed = GS > 4 ? v4i{0, 0, 0, 0} : v4i{kMagic, kMagic, kMagic, kMagic};
 
-  // Accumulator row r of lane (c, q) is output row 4 q + r; wave kq stores row
-  // 4 q + kq, whose alpha times out_scale is:
-  const int row = 4 * q + kq;
-  float oscale = 0.0f;
-  if constexpr (MQ > 0)
-    oscale = qa[min(row, M - 1)] * out_scale;
-  else if constexpr (!kPartials)
-    oscale = a_scale[min(row, M - 1)] * out_scale;
+  // Epilogue split: the TB x 4 pairs (token block u, accumulator row r) of
+  // every lane are dealt to the waves, pair x to wave x % W; pair (u, r) of
+  // lane (c, q) is output row 16 u + 4 q + r. With W = 4 and one token block,
+  // wave kq stores row 4 q + kq.
+  constexpr int NX = (4 * TB + W - 1) / W;  // pairs per wave
+  float oscale[NX];                         // alpha of the pair's row times out_scale
+#pragma unroll
+  for (int x = 0; x < NX; ++x) {
+    const int pi = kq + x * W;
+    const int row = 16 * (pi >> 2) + 4 * q + (pi & 3);
+    oscale[x] = 0.0f;
+    if constexpr (MQ > 0)
+      oscale[x] = qa[min(row, M - 1)] * out_scale;
+    else if constexpr (!kPartials)
+      oscale[x] = a_scale[min(row, M - 1)] * out_scale;
+  }
   // One-launch layer: every wave has read its codes before the loop's first
   // refill overwrites the scratch (the last ring slot).
   if constexpr (MQ > 0) __syncthreads();
@@ -310,9 +335,11 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
     const int blk = b_lo + tb * b_step;
     float bcol = 0.0f;  // beta of this lane's column, requested early
     if constexpr (!kPartials) bcol = w_scale[blk * kRows + c];
-    float f[4];
+    float f[TB][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) f[r] = 0.0f;
+    for (int u = 0; u < TB; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f[u][r] = 0.0f;
 #pragma unroll
     for (int sp = 0; sp < S::SPB; ++sp) {
       const int i = tb * S::SPB + sp;
@@ -345,76 +372,105 @@ __global__ __launch_bounds__(kThreads) void gemm_stream_kernel(
             ww[h][3] = 0u;
           }
         }
-        v4i acc = seed;
+        v4i acc[TB];
+#pragma unroll
+        for (int u = 0; u < TB; ++u) acc[u] = seed;
 #pragma unroll
         for (int st = 0; st < GS; ++st) {
           const int h = st >> 1;
           const int o = 2 * (st & 1);
           const v4i wv = unpack_pair(ww[h][o], ww[h][o + 1]);
-          acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(unpack_pair(aw[b][h][o], aw[b][h][o + 1]), wv,
-                                                      acc, 0, 0, 0);
+#pragma unroll
+          for (int u = 0; u < TB; ++u)
+            acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                unpack_pair(aw[u][b][h][o], aw[u][b][h][o + 1]), wv, acc[u], 0, 0, 0);
         }
         if constexpr (kPartials) {
           int32_t* Pg = P + (size_t)(kq * NG + b) * (size_t)M * (size_t)N;
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (4 * q + r < M)
-              Pg[(size_t)(4 * q + r) * N + blk * kRows + c] =
-                  (GS > 4 ? acc[r] : acc[r] - kMagic) >> 8;
+          for (int u = 0; u < TB; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int row = 16 * u + 4 * q + r;
+              if (row < M)
+                Pg[(size_t)row * N + blk * kRows + c] =
+                    (GS > 4 ? acc[u][r] : acc[u][r] - kMagic) >> 8;
+            }
         } else {
           const float s =
               __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sv), b));
-          // Bit-cast the whole vector, then index: bit-casting a single
-          // element of an ext_vector is miscompiled (every element reads
-          // element 0).
-          const v4f accf = __builtin_bit_cast(v4f, acc);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float pv = GS > 4 ? (float)acc[r] : accf[r] - 12582912.0f;
-            f[r] = __builtin_fmaf(s, pv, f[r]);
+          for (int u = 0; u < TB; ++u) {
+            // Bit-cast the whole vector, then index: bit-casting a single
+            // element of an ext_vector is miscompiled (every element reads
+            // element 0).
+            const v4f accf = __builtin_bit_cast(v4f, acc[u]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float pv = GS > 4 ? (float)acc[u][r] : accf[r] - 12582912.0f;
+              f[u][r] = __builtin_fmaf(s, pv, f[u][r]);
+            }
           }
         }
       }
     }
     if constexpr (!kPartials) {
-      // The four slices' sums of this block, added in the order kq = 0 .. 3.
+      // The W slices' sums of this block, added in the order kq = 0 .. W - 1.
       const int pb = PB == 2 ? (tb & 1) : 0;
-      part[pb][kq][lane] = v4f{f[0], f[1], f[2], f[3]};
-      __syncthreads();
-      float sum = part[pb][0][lane][kq];
 #pragma unroll
-      for (int p = 1; p < kWaves; ++p) sum += part[pb][p][lane][kq];
-      // out_scale = 2^-8 (undoes the 16 x 16 of the unpacked operands) / K
-      // (the unnormalized rotation; 1 without rotation), an exact power of two.
-      if (row < M)
-        Y[(size_t)row * N + blk * kRows + c] =
-            __builtin_bit_cast(uint16_t, (_Float16)((sum * oscale) * bcol));
+      for (int u = 0; u < TB; ++u) part[pb][kq][u][lane] = v4f{f[u][0], f[u][1], f[u][2], f[u][3]};
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < NX; ++x) {
+        const int pi = kq + x * W;
+        if (pi < 4 * TB) {
+          const int u = pi >> 2;
+          const int r = pi & 3;
+          float sum = part[pb][0][u][lane][r];
+#pragma unroll
+          for (int p = 1; p < W; ++p) sum += part[pb][p][u][lane][r];
+          const int row = 16 * u + 4 * q + r;
+          // out_scale = 2^-8 (undoes the 16 x 16 of the unpacked operands) / K
+          // (the unnormalized rotation; 1 without rotation), an exact power of two.
+          if (row < M)
+            Y[(size_t)row * N + blk * kRows + c] =
+                __builtin_bit_cast(uint16_t, (_Float16)((sum * oscale[x]) * bcol));
+        }
+      }
       if constexpr (PB == 1) __syncthreads();  // every wave has read `part`
     }
   }
 }
 
-// Shapes the kernel takes (K, g powers of two, g <= 512): every wave holds whole
-// groups (K >= 4 g); K = 16384 with g <= 128 keeps 32 or 64 groups of token codes
-// per wave, which do not fit the registers next to the loop.
-constexpr bool stream_form_fits(int K, int g) {
-  return K >= 4 * g && !(K == 16384 && g <= 128);
+// Shapes each form of the kernel takes (K, g powers of two, g <= 512).
+// W = 4, one token block: every wave holds whole groups (K >= 4 g); K = 16384
+// with g <= 128 keeps 32 or 64 groups of token codes per wave, which do not fit
+// the registers next to the loop. W = 8, two token blocks: K = 8192 only. The
+// form compiles without spills wherever K >= 1024, K >= 8 g and TB K <= 16384,
+// but it beats the few-token kernel only where the weight stream dominates:
+// at K = 8192, N = 28672, g = 128, cold weights, it takes 27.6 / 28.9 / 29.9 us at
+// M = 17 / 24 / 32 (row-major) against 36.2 / 37.8 / 38.7; at K = 4096, N = 12288
+// it ties up to 32 tokens and loses with three or four token blocks (13.7 against
+// 12.7 us at M = 64); at K = 8192 three or four token blocks spill.
+constexpr bool stream_form_fits(int K, int W, int TB, int g) {
+  return W == 4 ? (TB == 1 && K >= 4 * g && !(K == 16384 && g <= 128))
+                : (W == 8 && TB == 2 && K == 8192 && K >= 8 * g);
 }
 
-template <int K, bool kPartials>
+template <int K, int W, int TB, bool kPartials>
 hipError_t launch_k(const uint8_t* Xq, const float* a_scale, const float* s_group,
                     const uint8_t* Wq, const float* w_scale, int M, int N, int g, uint16_t* Y,
                     int32_t* P, float out_scale, hipStream_t stream, bool tiled) {
   const int nblk = N / kRows;  // N % 16 == 0 (API precondition)
 #define RRS_STREAM_T(GS_, T_)                                                              \
   {                                                                                        \
-    constexpr auto kern = gemm_stream_kernel<K, GS_, T_, kPartials>;                       \
-    kern<<<resident_grid<kern>(nblk), kThreads, 0, stream>>>(Xq, a_scale, s_group, Wq,      \
-                                                             w_scale, M, N, Y, P, out_scale, \
-                                                             nullptr);                      \
+    constexpr auto kern = gemm_stream_kernel<K, GS_, W, TB, T_, kPartials>;                \
+    kern<<<resident_grid<kern>(nblk, 64 * W), 64 * W, 0, stream>>>(Xq, a_scale, s_group,    \
+                                                                   Wq, w_scale, M, N, Y, P, \
+                                                                   out_scale, nullptr);     \
   }
 #define RRS_STREAM(GS_)                             \
-  if constexpr (stream_form_fits(K, GS_ * 64)) {    \
+  if constexpr (stream_form_fits(K, W, TB, GS_ * 64)) { \
     if (tiled)                                      \
       RRS_STREAM_T(GS_, true)                       \
     else                                            \
@@ -434,7 +490,7 @@ hipError_t launch_k(const uint8_t* Xq, const float* a_scale, const float* s_grou
   return hipGetLastError();
 }
 
-template <bool kPartials>
+template <int W, int TB, bool kPartials>
 hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_group,
                       const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
                       uint16_t* Y, int32_t* P, float out_scale, hipStream_t stream,
@@ -442,8 +498,8 @@ hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_gr
   switch (K) {
 #define RRS_K(K_)                                                                        \
   case K_:                                                                               \
-    return launch_k<K_, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, g, Y, P,       \
-                                   out_scale, stream, tiled)
+    return launch_k<K_, W, TB, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, g, Y, P, \
+                                          out_scale, stream, tiled)
     RRS_K(512);
     RRS_K(1024);
     RRS_K(2048);
@@ -455,21 +511,36 @@ hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_gr
   }
 }
 
+// The form for M tokens: up to 16, four waves and one token block; 17 to 32,
+// eight waves (one workgroup per compute unit) and two token blocks, so the
+// weights still stream once.
+template <bool kPartials>
+hipError_t launch_tokens(const uint8_t* Xq, const float* a_scale, const float* s_group,
+                         const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
+                         uint16_t* Y, int32_t* P, float out_scale, hipStream_t stream,
+                         bool tiled) {
+  if (M <= kMaxTokens)
+    return launch_any<4, 1, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, P,
+                                       out_scale, stream, tiled);
+  return launch_any<8, 2, kPartials>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, P,
+                                     out_scale, stream, tiled);
+}
+
 // The one-launch layer: the same kernel with the quantizer of MQ rows in
-// front of the loop.
+// front of the loop (four waves, one token block).
 template <int K, int MQ>
 hipError_t launch_layer_k(const uint16_t* X, const uint8_t* Wq, const float* w_scale, int N,
                           int g, uint16_t* Y, float out_scale, hipStream_t stream, bool tiled) {
   const int nblk = N / kRows;
 #define RRS_LAYER_T(GS_, T_)                                                                \
   {                                                                                         \
-    constexpr auto kern = gemm_stream_kernel<K, GS_, T_, false, MQ>;                        \
+    constexpr auto kern = gemm_stream_kernel<K, GS_, 4, 1, T_, false, MQ>;                  \
     kern<<<resident_grid<kern>(nblk), kThreads, 0, stream>>>(nullptr, nullptr, nullptr, Wq, \
                                                              w_scale, MQ, N, Y, nullptr,    \
                                                              out_scale, X);                 \
   }
 #define RRS_LAYER(GS_)                                 \
-  if constexpr (stream_form_fits(K, GS_ * 64)) {      \
+  if constexpr (stream_form_fits(K, 4, 1, GS_ * 64)) { \
     if (tiled)                                         \
       RRS_LAYER_T(GS_, true)                           \
     else                                               \
@@ -493,7 +564,7 @@ hipError_t launch_layer_k(const uint16_t* X, const uint8_t* Wq, const float* w_s
 
 bool layer_one_launch_fits(int M, int K, int g) {
   return (M == 1 || M == 2) && (K == 2048 || K == 4096 || K == 8192) &&
-         stream_form_fits(K, g);
+         stream_form_fits(K, 4, 1, g);
 }
 
 hipError_t launch_layer_one_launch(const uint16_t* X, int M, int N, int K, int g,
@@ -516,7 +587,9 @@ hipError_t launch_layer_one_launch(const uint16_t* X, int M, int N, int K, int g
 }
 
 bool stream_kernel_fits(int M, int K, int g) {
-  return M >= 1 && M <= kMaxTokens && stream_form_fits(K, g);
+  if (M < 1 || M > 2 * kMaxTokens) return false;
+  if (M <= kMaxTokens) return stream_form_fits(K, 4, 1, g);
+  return stream_form_fits(K, 8, 2, g);
 }
 
 hipError_t launch_w4a4_gemm_stream(const uint8_t* Xq, const float* a_scale,
@@ -525,7 +598,7 @@ hipError_t launch_w4a4_gemm_stream(const uint8_t* Xq, const float* a_scale,
                                    uint16_t* Y, float out_scale, hipStream_t stream,
                                    WqLayout lay) {
   if (!stream_kernel_fits(M, K, g)) return hipErrorInvalidValue;
-  return launch_any<false>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, nullptr,
+  return launch_tokens<false>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y, nullptr,
                               out_scale, stream, lay.tiled);
 }
 
@@ -533,7 +606,7 @@ hipError_t launch_w4a4_gemm_stream_partials(const uint8_t* Xq, const uint8_t* Wq
                                             int K, int g, int32_t* P, hipStream_t stream,
                                             WqLayout lay) {
   if (!stream_kernel_fits(M, K, g)) return hipErrorInvalidValue;
-  return launch_any<true>(Xq, nullptr, nullptr, Wq, nullptr, M, N, K, g, nullptr, P, 0.0f,
+  return launch_tokens<true>(Xq, nullptr, nullptr, Wq, nullptr, M, N, K, g, nullptr, P, 0.0f,
                              stream, lay.tiled);
 }
 

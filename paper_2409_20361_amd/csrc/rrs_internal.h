@@ -129,10 +129,23 @@ hipError_t launch_w4a4_gemm_partials_small(const uint8_t* Xq, const uint8_t* Wq,
                                            int N, int K, int g, int32_t* P,
                                            hipStream_t stream, WqLayout lay = {false});
 
-// Few-token kernel (decode): streams Wq once, for M <= 16, with or without the
-// runtime reorder.
-bool decode_kernel_fits(int M);
-bool decode_gather_fits(int M);
+// The kernel of a GEMM call (rrs_gemm_route.cpp). `scratch`: whether the caller has
+// the memory of fp6_scratch_bytes; without it the 6-bit paths are not chosen.
+enum class GemmPath {
+  kStream, kStreamGather, kDecode, kDecodeGather, kMid, kMain,
+  kFp6Teams, kFp6Small, kFp6Large, kFp6Tail
+};
+struct GemmCall {
+  int M, N, K, g;  // g is not read with per_channel
+  bool per_channel, reorder, tiled;
+};
+GemmPath gemm_path(const GemmCall& c, bool scratch);
+inline bool on_scratch(GemmPath p) { return p >= GemmPath::kFp6Teams; }
+const char* gemm_path_name(GemmPath p);
+
+// Few-token kernel (decode): streams Wq once, for M <= 16 with or without the
+// runtime reorder, and for M <= 64 in the forms of decode_wide_fits.
+bool decode_wide_fits(int M, int K, int g, bool tiled);
 // Runtime-reorder GEMM on the weight stream (rrs_gemm_stream.hip): up to 16
 // tokens, K <= 8192, any g, either layout.
 bool stream_gather_fits(int M, int K);
@@ -151,7 +164,7 @@ hipError_t launch_w4a4_gemm_decode_partials(const uint8_t* Xq, const uint8_t* Wq
                                             int K, int g, int32_t* P, hipStream_t stream);
 
 // 17 to a few hundred tokens (rrs_gemm_mid.hip): small tiles whose waves split
-// K. mid_kernel_fits says where it beats the main kernel; it takes any M.
+// K. mid_kernel_fits says where it may beat the main kernel; it takes any M.
 bool mid_kernel_fits(int M, int N);
 hipError_t launch_w4a4_gemm_mid(const uint8_t* Xq, const float* a_scale, const float* s_group,
                                 const uint8_t* Wq, const float* w_scale, const int32_t* border,
@@ -170,15 +183,17 @@ hipError_t launch_w4a4_gemm_mid_partials(const uint8_t* Xq, const uint8_t* Wq, i
 // fp6_scratch_bytes is 0 where another kernel serves. s_group == nullptr:
 // per-channel (border must be nullptr too).
 size_t fp6_scratch_bytes(int M, int N, int K);
-hipError_t launch_w4a4_gemm_fp6(const uint8_t* Xq, const float* a_scale, const float* s_group,
+GemmPath fp6_form(int M, int N, int K);  // the tiles it takes there
+hipError_t launch_w4a4_gemm_fp6(GemmPath path, const uint8_t* Xq, const float* a_scale, const float* s_group,
                                 const uint8_t* Wq, const float* w_scale, const int32_t* border,
                                 int M, int N, int K, int g, uint16_t* Y, float out_scale,
                                 void* scratch, hipStream_t stream, WqLayout lay);
 
 // Weight-streaming kernel for few tokens (rrs_gemm_stream.hip): each
 // workgroup copies 16 whole rows of Wq into LDS with direct-to-LDS loads.
-// Up to 16 tokens, K >= 4 g (not K = 16384 with g <= 128). Both layouts,
-// bit-identical results.
+// Up to 16 tokens: four waves, K >= 4 g (not K = 16384 with g <= 128). 17 to
+// 32 tokens at K = 8192: eight waves and two blocks of 16 tokens. Both
+// layouts, bit-identical results.
 bool stream_kernel_fits(int M, int K, int g);
 hipError_t launch_w4a4_gemm_stream(const uint8_t* Xq, const float* a_scale,
                                    const float* s_group, const uint8_t* Wq,
