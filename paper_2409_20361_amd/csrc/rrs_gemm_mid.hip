@@ -308,6 +308,8 @@ hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
   return hipGetLastError();
 }
 
+}  // namespace
+
 // Token blocks per tile: the largest tile that still gives 160 workgroups (a
 // little over half of the compute units; below that a smaller tile's second
 // pass over the weights, out of L2, costs less than the idle units). Measured,
@@ -315,7 +317,7 @@ hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
 // us (80 / 160 / 304 workgroups); 64 x 4096 x 4096 10.5 / 8.1 / 7.1 (64 / 128 /
 // 256); 32 x 16384 x 4096 - / 24.2 / 20.8 (64 / 128); 32 x 4096 x 12288 - / 8.4 /
 // 11.4 (192 / 384); 173 x 4096 x 4096 11.1 / 13.9 / 16.1 (192 / 384 / 704).
-int token_blocks(int M, int N) {
+int mid_token_blocks(int M, int N) {
   const int tn = (N + BN - 1) / BN;
   for (int rb = 4; rb > 1; rb /= 2) {
     if (M <= 8 * rb) continue;  // half of the tile would be idle
@@ -324,12 +326,14 @@ int token_blocks(int M, int N) {
   return 1;
 }
 
+namespace {
+
 template <Mode mode, bool kGather, bool kTiled>
 hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_group,
                       const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
                       uint16_t* Y, int32_t* P, float out_scale, hipStream_t stream,
                       const int32_t* border) {
-  const int rb = token_blocks(M, N);
+  const int rb = mid_token_blocks(M, N);
 #define RRS_MID(GS_, RB_)                                                                       \
   launch<GS_, RB_, mode, kGather, kTiled>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, P, \
                                           out_scale, stream, border)

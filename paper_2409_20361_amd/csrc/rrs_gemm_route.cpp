@@ -35,6 +35,90 @@ bool decode_wide(const GemmCall& c) {
   return c.K == 4096 || (c.K == 2048 && c.N > 64 * 191);
 }
 
+// Time of a call in us (the launch that spreads the tokens included), to compare a
+// path with the main kernel. A kernel works off its tiles in rounds over the compute
+// units, `cap` tiles per XCD and round; a round takes a time per K tile of 128, by the
+// group size (a column each for 64, 128, 256, 512 and per-channel), more with gathered
+// row-major weights (pieces of 16 bytes) and, for the 6-bit paths, with the tiled layout
+// (its 16-byte pieces are spread by other lanes). Output and token terms are per
+// million elements. Fitted by least squares to 4000 calls with 65 to 8192 tokens, all of
+// whose paths were measured: 4 to 8 % off (mid-size 13 %). With the comparison 76 of them
+// are more than 2 % slower than the main kernel, without it 621, most of them with few
+// columns or K up to 2048, where the token launch costs more than 6-bit operands
+// save: 4096 x 2048 x 1120 (M x K x N) 21.3 us on the main kernel, 24.9 with two teams.
+struct Fit {
+  double tile[5], gather64, gather, tiled;  // per K tile of a round, and shares on top
+  double fixed, out, tokens, round;
+  double last, share, half;  // the last round: last + share x its filling (half: up to half)
+};
+constexpr Fit kMainFit = {{1.457, 1.083, 0.948, 0.873, 0.787}, 0.045, 0.092, 0, 3.45, 0.239, 0,
+                          2.53, 0.801, 0.146, 0};
+constexpr Fit kTeamsFit = {{0.559, 0.459, 0.451, 0.476, 0.436}, 0.34, 0.63, 0.055, 3.35, 0.671,
+                           0.12, 4.46, 0.877, 0.141, 0};
+constexpr Fit kSmallFit = {{1.03, 0.871, 0.819, 0.861, 0.784}, 0.359, 0.402, 0.12, 5.28, 0.288,
+                           0.211, 1.70, 1.099, 0, 0.759};
+constexpr Fit kLargeFit = {{1.026, 0.818, 0.806, 0.821, 0.735}, 0.191, 0.254, 0.011, 6.48, 0.249,
+                           0.143, 2.03, 0.794, 0.184, 0};
+constexpr Fit kTailFit = {{0.946, 0.768, 0.752, 0.767, 0.697}, 0.218, 0.334, 0.029, 8.41, 0.364,
+                          0.185, 1.44, 0.479, 0.317, 0};
+
+int ceil_div(int a, int b) { return (int)(((long)a + b - 1) / b); }
+
+double fit_us(const Fit& f, const GemmCall& c, int bm, int cap) {
+  const long tiles = (long)ceil_div(c.M, bm) * ceil_div(c.N, 128);
+  const long per = (tiles + 7) / 8;
+  const double full = (double)(per / cap), rest = (double)(per % cap) / cap;
+  const double last = rest == 0 ? 0 : f.half > 0 && rest <= 0.5 ? f.half : f.last + f.share * rest;
+  const int col = c.per_channel ? 4 : c.g == 64 ? 0 : c.g == 128 ? 1 : c.g == 256 ? 2 : 3;
+  double tile = f.tile[col];
+  if (c.reorder && !c.tiled) tile *= 1 + (c.g == 64 ? f.gather64 : f.gather);
+  if (c.tiled) tile *= 1 + f.tiled;
+  return f.fixed + 1e-6 * c.M * (f.out * c.N + f.tokens * c.K) + f.round * (full + (rest > 0)) +
+         tile * (full + last) * (c.K / 128);
+}
+
+// The mid-size kernel: two tiles per compute unit. K tiles between the mean and the
+// longest wave's (waves without any leave the others more), and 3.4 for the start and
+// the sum; row-major weights cost more the fewer tokens share them, gathered ones once
+// the caches no longer hold them.
+double mid_us(const GemmCall& c) {
+  const int rb = mid_token_blocks(c.M, c.N);
+  const int i = rb == 4 ? 0 : rb == 2 ? 1 : 2;
+  constexpr double kTile[3] = {0.313, 0.175, 0.145}, kRow[3] = {0.336, 0.564, 0.777};
+  const long per = ((long)ceil_div(c.M, 16 * rb) * ceil_div(c.N, 64) + 7) / 8;
+  const double full = (double)(per / 64), rest = (double)(per % 64) / 64;
+  const int run = !c.per_channel && c.g > 128 ? c.g / 128 : 1;  // K tiles of a wave's turn
+  const double kt = 0.545 * (c.K / 128) + 0.455 * 4 * run * ceil_div(c.K / 128 / run, 4) + 3.37;
+  const double k = c.K < 4096 ? c.K / 4096.0 : 1.0;
+  double tile = kTile[i];
+  if (!c.per_channel && c.g == 64) tile *= 1.68;
+  if (!c.tiled) tile *= 1 + kRow[i];
+  if (c.reorder && !c.tiled) tile *= 1 + 0.413 * k * k;
+  return 2.39 + 1.104e-6 * c.M * c.N +
+         tile * kt * (full + (rest > 0 ? 0.326 + 0.773 * rest : 0));
+}
+
+double path_us(GemmPath p, const GemmCall& c) {
+  switch (p) {
+    case GemmPath::kMid: return mid_us(c);
+    case GemmPath::kFp6Teams: return fit_us(kTeamsFit, c, 128, 32);
+    case GemmPath::kFp6Small: return fit_us(kSmallFit, c, 128, 64);
+    case GemmPath::kFp6Large: return fit_us(kLargeFit, c, 256, 32);
+    case GemmPath::kFp6Tail: return fit_us(kTailFit, c, 256, 32);
+    default: return fit_us(kMainFit, c, 256, 32);
+  }
+}
+
+GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
+  // Two workgroups of 128 x 128 per compute unit gather row-major weights for twice the
+  // tiles, and from K = 4096 the caches no longer hold them: 547 x 8192 x 23696, g = 256,
+  // 328 us, main 207; 548 x 4096 x 22016, g = 512, 142 / 104; 1020 x 4096 x 12288, g = 256,
+  // 80 / 78. (g = 64, where the main kernel is slowest, stays: 1867 x 8192 x 8512 231 / 278.)
+  if (p == GemmPath::kFp6Small && c.reorder && !c.tiled && c.K >= 4096 && c.g >= 128)
+    return GemmPath::kMain;
+  return path_us(GemmPath::kMain, c) < path_us(p, c) ? GemmPath::kMain : p;
+}
+
 }  // namespace
 
 GemmPath gemm_path(const GemmCall& c, bool scratch) {
@@ -54,8 +138,8 @@ GemmPath gemm_path(const GemmCall& c, bool scratch) {
   // Without the rescale the mid-size kernel stays ahead where it fits (300 x 8192 x
   // 8192: 33 against 35.5 us).
   if (scratch && fp6_scratch_bytes(c.M, c.N, c.K) && !(c.per_channel && mid))
-    return fp6_form(c.M, c.N, c.K);
-  return mid ? GemmPath::kMid : GemmPath::kMain;
+    return unless_main_is_faster(fp6_form(c.M, c.N, c.K), c);
+  return mid ? unless_main_is_faster(GemmPath::kMid, c) : GemmPath::kMain;
 }
 
 const char* gemm_path_name(GemmPath p) {

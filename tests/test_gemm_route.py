@@ -26,6 +26,29 @@ def test_few_tokens(M, K, N, g, tiled, path):
         assert rrs.gemm_path(M, N, K, g, flags, scratch=scratch) == path
 
 
+@pytest.mark.parametrize("M,K,N,g,kind,tiled,path", [
+    # the main kernel where the token launch or idle tiles cost more than they save
+    (4096, 2048, 1120, 128, None, False, "main"), (8192, 2048, 608, 512, None, True, "main"),
+    (5953, 1024, 992, 128, None, True, "main"), (2048, 1024, 4096, 128, "per_channel", False, "main"),
+    (2048, 4096, 4096, 128, "per_channel", False, "main"),
+    (5346, 2048, 784, 64, "per_channel", False, "main"),
+    (8192, 2048, 1024, 512, "reorder", False, "main"),
+    (547, 8192, 23696, 256, "reorder", False, "main"), (89, 512, 22016, 512, None, False, "main"),
+    # and the others where they are ahead
+    (173, 4096, 4096, 128, None, False, "mid"), (512, 8192, 8192, 128, None, False, "fp6_teams"),
+    (1024, 4096, 12288, 128, "per_channel", False, "fp6_small"),
+    (1500, 4096, 12288, 128, "reorder", False, "fp6_tail"),
+    (2048, 4096, 12288, 128, None, False, "fp6_large"),
+    (1867, 8192, 8512, 64, "reorder", False, "fp6_small"),
+])
+def test_many_tokens(M, K, N, g, kind, tiled, path):
+    flags = rrs.WEIGHT_TILED if tiled else 0
+    forms = {kind: True} if kind else {}
+    assert rrs.gemm_path(M, N, K, g, flags, **forms) == path
+    if path in ("main", "mid"):  # also the calls without scratch
+        assert rrs.gemm_path(M, N, K, g, flags, scratch=False, **forms) == path
+
+
 def test_other_forms_have_no_wide_few_token_kernel():
     for M, K, N, g in ((24, 8192, 1024, 128), (32, 16384, 12288, 512), (48, 512, 28672, 64)):
         for kind in ("reorder", "per_channel"):
