@@ -55,6 +55,14 @@ constexpr int BN = 16 * kCB;
 constexpr int kRedStride = BN + 4;
 constexpr int kMagic = 0x4B400000;  // bits of 1.5 * 2^23
 
+// fp16(a b) with one rounding, as every other kernel stores: the compiler folds their
+// conversion into the product, but not where two halves are packed.
+__device__ __forceinline__ uint16_t half_once(float a, float b) {
+  uint32_t h;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(a), "v"(b));
+  return (uint16_t)h;
+}
+
 enum Mode { kSmooth, kPerChannel, kPartials };
 
 // GS = g / 32; RB blocks of 16 tokens. kGather (runtime channel reorder):
@@ -291,7 +299,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
       uint16_t h[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        h[e] = __builtin_bit_cast(uint16_t, (_Float16)((sum[e] * sc) * bc[e]));
+        h[e] = half_once(sum[e] * sc, bc[e]);
       *reinterpret_cast<v2u*>(Y + (size_t)gr * N + gc) =
           v2u{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
     }

@@ -39,3 +39,23 @@ def test_wide(M, K, N, g, tiled, path):
     Y = rrs.w4a4_gemm(X, to_gpu(a), to_gpu(s), to_gpu(tile_wq(rows) if tiled else rows),
                       to_gpu(b), g, flags=fl)
     _check(to_np(Y), P, a, s, b, K, path)
+
+
+@pytest.mark.parametrize("M,K,N,paths", [
+    (663, 1024, 4336, ("main", "mid")), (757, 2048, 5264, ("fp6_teams", "main")),
+    (788, 1024, 12912, ("fp6_small", "main"))])
+def test_per_channel_bits_on_any_kernel(M, K, N, paths):
+    # One exact sum and one rounding: the kernel, which here depends on the layout, does not.
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_20361_amd as rrs
+    print(f"[case] per-channel bits M={M} K={K} N={N}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    Xq = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device="cuda", generator=gen)
+    a = torch.rand(M, device="cuda", generator=gen) * 1e-2
+    W = (0.02 * torch.randn((K, N), generator=gen, device="cuda")).half()
+    Y = []
+    for flags, path in zip((0, rrs.WEIGHT_TILED), paths):
+        assert rrs.gemm_path(M, N, K, 128, flags, per_channel=True) == path
+        Y.append(rrs.w4a4_gemm_per_channel(Xq, a, *rrs.prepare_weight(W, None, flags), flags=flags))
+    assert torch.equal(*Y)
