@@ -508,7 +508,7 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
 size_t rrs_gemm_scratch_bytes(int M, int N, int K);
 
 /* Test hook: the name of the kernel a GEMM call takes, a host query ("stream",
- * "stream_gather", "decode", "decode_gather", "mid", "main", "fp6_teams", "fp6_small",
+ * "stream_gather", "decode", "decode_gather", "mid", "mid_eighths", "main", "fp6_teams", "fp6_small",
  * "fp6_large", "fp6_tail"; "" for invalid arguments). scheme:
  * RRS_SCHEME_RUNTIME_SMOOTH or RRS_SCHEME_PER_CHANNEL (group_size then not read);
  * reorder: with block_order; scratch: with rrs_gemm_scratch_bytes of scratch. */

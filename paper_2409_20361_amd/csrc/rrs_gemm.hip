@@ -463,6 +463,9 @@ hipError_t launch_w4a4_gemm(const uint8_t* Xq, const float* a_scale, const float
     case GemmPath::kMid:
       return launch_w4a4_gemm_mid(Xq, a_scale, s_group, Wq, w_scale, nullptr, M, N, K, g, Y,
                                   out_scale, stream, lay);
+    case GemmPath::kMidEighths:
+      return launch_w4a4_gemm_mid_eighths(Xq, a_scale, s_group, Wq, w_scale, M, N, K, g, Y,
+                                          out_scale, stream);
     default: break;
   }
   if (!main_kernel_fits(K, g))
@@ -524,7 +527,7 @@ hipError_t launch_w4a4_gemm_partials(const uint8_t* Xq, const uint8_t* Wq, int M
   // The kernel rrs_w4a4_gemm takes for this shape; the hooks of the few-token and
   // mid-size kernels read a row-major Wq.
   const GemmPath p = gemm_path({M, N, K, g, false, false, lay.tiled}, false);
-  if (p == GemmPath::kStream)
+  if (p == GemmPath::kStream || p == GemmPath::kMidEighths)
     return launch_w4a4_gemm_stream_partials(Xq, Wq, M, N, K, g, P, stream, lay);
   if (p == GemmPath::kDecode && !lay.tiled)
     return launch_w4a4_gemm_decode_partials(Xq, Wq, M, N, K, g, P, stream);

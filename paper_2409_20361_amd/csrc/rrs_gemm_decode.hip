@@ -457,12 +457,11 @@ __global__ __launch_bounds__(kThreads) void gemm_decode_gather_kernel(
 
 }  // namespace
 
-// Above 16 tokens, the forms the route takes (rrs_gemm_route.cpp): long groups, or
-// two groups of 64 per wave (K = 512).
-bool decode_wide_fits(int M, int K, int g, bool tiled) {
+// Above 16 tokens, the forms that are compiled: long groups, or two groups of 64 per
+// wave (K = 512) above 32 tokens.
+bool decode_wide_fits(int M, int K, int g) {
   if (M <= kCols || M > kCols * kMaxTokenBlocks) return false;
-  if (M > 2 * kCols) return (g >= 256 && !tiled) || (g == 64 && K == 512);
-  return g >= 256 && (g == 512 || !tiled);
+  return g >= 256 || (g == 64 && K == 512 && M > 2 * kCols);
 }
 
 namespace {
@@ -492,10 +491,10 @@ hipError_t launch_gs(const uint8_t* Xq, const float* a_scale, const float* s_gro
       if (M >= 8) RRS_DECODE(1, 4);
     RRS_DECODE(1, kBlocks);
   }
-  if (!decode_wide_fits(M, K, GS * 64, kTiled)) return hipErrorInvalidValue;
-  if constexpr (GS == 8 || (GS == 4 && !kTiled))
+  if (!decode_wide_fits(M, K, GS * 64)) return hipErrorInvalidValue;
+  if constexpr (GS >= 4)
     if (M <= 2 * kCols) RRS_DECODE(2, 4);
-  if constexpr (GS == 1 || (GS >= 4 && !kTiled)) RRS_DECODE(4, 4);
+  if constexpr (GS == 1 || GS >= 4) RRS_DECODE(4, 4);
   return hipErrorInvalidValue;
 #undef RRS_DECODE
 }

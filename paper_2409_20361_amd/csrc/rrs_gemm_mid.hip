@@ -66,8 +66,10 @@ __device__ __forceinline__ uint16_t half_once(float a, float b) {
 enum Mode { kSmooth, kPerChannel, kPartials };
 
 // GS = g / 32; RB blocks of 16 tokens. kGather (runtime channel reorder):
-// position block p of Xq pairs with block border[p] of every Wq row.
-template <int GS, int RB, Mode mode, bool kGather, bool kTiled>
+// position block p of Xq pairs with block border[p] of every Wq row. kEighths: wave w
+// takes the contiguous eighths 2 w and 2 w + 1 of K instead, and the eight sums are
+// added in their order, which is the eight-wave weight stream's: the same bits.
+template <int GS, int RB, Mode mode, bool kGather, bool kTiled, bool kEighths>
 __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
     const uint8_t* __restrict__ Xq, const float* __restrict__ a_scale,
     const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
@@ -76,7 +78,8 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
   constexpr WqLayout lay{kTiled};
   constexpr int BM = 16 * RB;
   constexpr int TPG = GS > 4 ? GS / 4 : 1;  // K tiles of 128 per group
-  __shared__ __attribute__((aligned(16))) float red[NW * BM * kRedStride];
+  constexpr int kParts = kEighths ? 2 * NW : NW;
+  __shared__ __attribute__((aligned(16))) float red[kParts * BM * kRedStride];
   __shared__ int btab[kGather ? 16384 / kReorderBlock : 1];
 
   const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
@@ -93,6 +96,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
   const int n = wave < ng ? TPG * ((ng - wave + NW - 1) / NW) : 0;
   auto tile_of = [&](int i) {
     i = min(i, max(n - 1, 0));
+    if constexpr (kEighths) return wave * n + i;  // n = K / 512
     return min((wave + i / TPG * NW) * TPG + i % TPG, K / 128 - 1);
   };
 
@@ -251,11 +255,29 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
     load_b(d, d);
     load_a(d, d);
   }
+  auto put = [&](int part) {  // a wave's sums to LDS
+    float* mine = red + part * BM * kRedStride;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < kCB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine[(16 * i + 4 * q + e) * kRedStride + 16 * j + r] = f[i][j][e];
+  };
   // Trips of U tiles; the last one requests nothing past itself. Tiles past a
   // wave's last repeat it and count with scale 0.
   constexpr int U = TPG > DB ? TPG : DB;
   int i0 = 0;
   for (; i0 + U < n; i0 += U) {
+    if constexpr (kEighths) {
+      if (i0 == n / 2) {  // a trip's start: n is a multiple of 2 U
+        put(2 * wave);
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int j = 0; j < kCB; ++j) f[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       compute(u, i0 + u);
@@ -277,13 +299,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
   if constexpr (mode == kPartials) return;
 
   // The waves' sums are added in a fixed order through LDS.
-  float* mine = red + wave * BM * kRedStride;
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-#pragma unroll
-    for (int j = 0; j < kCB; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) mine[(16 * i + 4 * q + e) * kRedStride + 16 * j + r] = f[i][j][e];
+  put(kEighths ? 2 * wave + 1 : wave);
   __syncthreads();
   constexpr int kPieces = BM * BN / 4;
 #pragma unroll
@@ -291,7 +307,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
     const int row = p >> 4, c4 = (p & 15) * 4;
     v4f sum = *reinterpret_cast<const v4f*>(red + row * kRedStride + c4);
 #pragma unroll
-    for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const v4f*>(red + (w * BM + row) * kRedStride + c4);
+    for (int w = 1; w < kParts; ++w) sum += *reinterpret_cast<const v4f*>(red + (w * BM + row) * kRedStride + c4);
     const int gr = m0 + row, gc = n0 + c4;
     if (gr < M && gc < N) {
       const float sc = a_scale[gr] * out_scale;
@@ -306,12 +322,12 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
   }
 }
 
-template <int GS, int RB, Mode mode, bool kGather, bool kTiled>
+template <int GS, int RB, Mode mode, bool kGather, bool kTiled, bool kEighths = false>
 hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
                   const uint8_t* Wq, const float* w_scale, int M, int N, int K, uint16_t* Y,
                   int32_t* P, float out_scale, hipStream_t stream, const int32_t* border) {
   const int T = ((M + 16 * RB - 1) / (16 * RB)) * ((N + BN - 1) / BN);
-  gemm_mid_kernel<GS, RB, mode, kGather, kTiled><<<8 * ((T + 7) / 8), 64 * NW, 0, stream>>>(
+  gemm_mid_kernel<GS, RB, mode, kGather, kTiled, kEighths><<<8 * ((T + 7) / 8), 64 * NW, 0, stream>>>(
       Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, P, out_scale, border);
   return hipGetLastError();
 }
@@ -390,6 +406,24 @@ hipError_t launch_w4a4_gemm_mid(const uint8_t* Xq, const float* a_scale, const f
                                                       Y, nullptr, out_scale, stream, nullptr)
                    : launch_any<kSmooth, false, false>(Xq, a_scale, s_group, Wq, w_scale, M, N, K,
                                                        g, Y, nullptr, out_scale, stream, nullptr);
+}
+
+hipError_t launch_w4a4_gemm_mid_eighths(const uint8_t* Xq, const float* a_scale,
+                                        const float* s_group, const uint8_t* Wq,
+                                        const float* w_scale, int M, int N, int K, int g,
+                                        uint16_t* Y, float out_scale, hipStream_t stream) {
+  if (K != 8192 || M > 32) return hipErrorInvalidValue;
+  const int rb = mid_token_blocks(M, N);
+#define RRS_MID(GS_, RB_)                                                                     \
+  launch<GS_, RB_, kSmooth, false, true, true>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, \
+                                               nullptr, out_scale, stream, nullptr)
+  switch (g) {
+    case 64: return rb == 2 ? RRS_MID(2, 2) : RRS_MID(2, 1);
+    case 128: return rb == 2 ? RRS_MID(4, 2) : RRS_MID(4, 1);
+    case 256: return rb == 2 ? RRS_MID(8, 2) : RRS_MID(8, 1);
+    default: return hipErrorInvalidValue;
+  }
+#undef RRS_MID
 }
 
 hipError_t launch_w4a4_gemm_mid_per_channel(const uint8_t* Xq, const float* a_scale,

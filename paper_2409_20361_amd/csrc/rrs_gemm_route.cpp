@@ -7,32 +7,34 @@
 namespace rrs {
 namespace {
 
+// Both layouts of the weights give the same bits, so a choice between kernels that add
+// the groups' sums in different orders goes by sizes and options alone. (The main kernel
+// and the 6-bit kernel's one-team forms add in the same order, and the per-channel scheme
+// has no such sum.)
+
 // 17 to 32 tokens at K = 8192: the eight-wave weight stream reads whole rows of
-// 512 bytes per wave, where the mid-size kernel's loads take 64 bytes of each of 16
-// rows. Row-major it is ahead (stream / mid, 32 tokens, g = 128: N = 1024 8.1 / 11.6,
-// 12288 16.5 / 18.4, 28672 29.9 / 36.0; the two tie at N = 16384). With the tiled layout both read
-// contiguous tiles: it is ahead where there are few columns, g = 512 (the mid-size
-// kernel then converts its sums) or the second block of tokens nearly empty.
-bool stream_wide(const GemmCall& c) {
-  if (c.M > 32 || c.K != 8192) return false;
-  if (!c.tiled) return true;
-  if (c.g == 512) return c.N <= 4096 || c.N >= 10240 || c.M <= 20;
-  return c.N <= 4096 && (c.g == 128 || c.M <= 24);
-}
+// 512 bytes per wave, where the mid-size kernel's row-major loads take 64 bytes of each of
+// 16 rows. Stream / mid, 32 tokens, g = 128: N = 1024 8.1 / 11.6, 12288 16.5 / 18.4,
+// 28672 29.9 / 36.0 (a tie at N = 16384). With the tiled layout both read contiguous tiles,
+// and from some 6000 columns on the mid-size kernel is ahead (N = 28672 29.7 / 27.3; not
+// with g = 512, whose sums it converts): its form by eighths of K, with the stream's bits.
+bool stream_wide(const GemmCall& c) { return c.M <= 32 && c.K == 8192; }
+bool mid_eighths(const GemmCall& c) { return c.tiled && c.N >= 6144 && c.g <= 256; }
 
 // 17 to 64 tokens, long groups, from the width on where the mid-size kernel's tiles
 // are 32 tokens and more (160 tiles of columns): a wave of the few-token kernel reads
 // a group of a row at once, 128 or 256 bytes, and the mid-size kernel 64. Few-token /
 // mid, row-major, g = 256, N = 12288: 32 x 4096 9.7 / 10.5, 32 x 16384 28.4 / 34.7, 64 x
-// 16384 38.0 / 42.7; g = 512, tiled, 32 x 16384 x 20480 46.5 / 47.8. With two groups of
-// 64 per wave (K = 512) the mid-size kernel's prologue and sum are all there is: 64 x
-// 512 x 20480 9.1 / 11.4.
+// 16384 38.0 / 42.7 (tiled between 5 % ahead and 13 % behind). With two groups of 64 per
+// wave (K = 512) the mid-size kernel's prologue and sum are all there is: 64 x 512 x 20480
+// 9.1 / 11.4. At K = 2048 the line is where the mean of both layouts turns.
 bool decode_wide(const GemmCall& c) {
-  if (!decode_wide_fits(c.M, c.K, c.g, c.tiled) || c.N <= 64 * 159) return false;
+  const int columns = (c.N + 63) / 64;
+  if (!decode_wide_fits(c.M, c.K, c.g) || columns < 160) return false;
   if (c.K == 512) return c.g == 64;
   if (c.K == 16384) return true;
-  if (c.tiled || c.M > 32) return false;
-  return c.K == 4096 || (c.K == 2048 && c.N > 64 * 191);
+  if (c.M > 32) return false;
+  return c.K == 4096 || (c.K == 2048 && columns >= (c.g == 512 ? 192 : 320));
 }
 
 // Time of a call in us (the launch that spreads the tokens included), to compare a
@@ -109,6 +111,14 @@ double path_us(GemmPath p, const GemmCall& c) {
   }
 }
 
+// The mean over both layouts, for a choice that must not depend on it.
+double both_layouts_us(GemmPath p, GemmCall c) {
+  c.tiled = !c.tiled;
+  const double other = path_us(p, c);
+  c.tiled = !c.tiled;
+  return (path_us(p, c) + other) / 2;
+}
+
 GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
   // Two workgroups of 128 x 128 per compute unit gather row-major weights for twice the
   // tiles, and from K = 4096 the caches no longer hold them: 547 x 8192 x 23696, g = 256,
@@ -116,7 +126,11 @@ GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
   // 80 / 78. (g = 64, where the main kernel is slowest, stays: 1867 x 8192 x 8512 231 / 278.)
   if (p == GemmPath::kFp6Small && c.reorder && !c.tiled && c.K >= 4096 && c.g >= 128)
     return GemmPath::kMain;
-  return path_us(GemmPath::kMain, c) < path_us(p, c) ? GemmPath::kMain : p;
+  const bool same_order =
+      c.per_channel || p == GemmPath::kFp6Small || p == GemmPath::kFp6Large;
+  const bool main = same_order ? path_us(GemmPath::kMain, c) < path_us(p, c)
+                               : both_layouts_us(GemmPath::kMain, c) < both_layouts_us(p, c);
+  return main ? GemmPath::kMain : p;
 }
 
 }  // namespace
@@ -131,7 +145,7 @@ GemmPath gemm_path(const GemmCall& c, bool scratch) {
     return stream_kernel_fits(c.M, c.K, c.g) ? GemmPath::kStream : GemmPath::kDecode;
   }
   if (!c.per_channel && !c.reorder) {
-    if (stream_wide(c)) return GemmPath::kStream;
+    if (stream_wide(c)) return mid_eighths(c) ? GemmPath::kMidEighths : GemmPath::kStream;
     if (decode_wide(c)) return GemmPath::kDecode;
   }
   const bool mid = mid_kernel_fits(c.M, c.N);
@@ -149,6 +163,7 @@ const char* gemm_path_name(GemmPath p) {
     case GemmPath::kDecode: return "decode";
     case GemmPath::kDecodeGather: return "decode_gather";
     case GemmPath::kMid: return "mid";
+    case GemmPath::kMidEighths: return "mid_eighths";
     case GemmPath::kMain: return "main";
     case GemmPath::kFp6Teams: return "fp6_teams";
     case GemmPath::kFp6Small: return "fp6_small";

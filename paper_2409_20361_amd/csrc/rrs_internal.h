@@ -132,7 +132,7 @@ hipError_t launch_w4a4_gemm_partials_small(const uint8_t* Xq, const uint8_t* Wq,
 // The kernel of a GEMM call (rrs_gemm_route.cpp). `scratch`: whether the caller has
 // the memory of fp6_scratch_bytes; without it the 6-bit paths are not chosen.
 enum class GemmPath {
-  kStream, kStreamGather, kDecode, kDecodeGather, kMid, kMain,
+  kStream, kStreamGather, kDecode, kDecodeGather, kMid, kMidEighths, kMain,
   kFp6Teams, kFp6Small, kFp6Large, kFp6Tail
 };
 struct GemmCall {
@@ -145,7 +145,7 @@ const char* gemm_path_name(GemmPath p);
 
 // Few-token kernel (decode): streams Wq once, for M <= 16 with or without the
 // runtime reorder, and for M <= 64 in the forms of decode_wide_fits.
-bool decode_wide_fits(int M, int K, int g, bool tiled);
+bool decode_wide_fits(int M, int K, int g);
 // Runtime-reorder GEMM on the weight stream (rrs_gemm_stream.hip): up to 16
 // tokens, K <= 8192, any g, either layout.
 bool stream_gather_fits(int M, int K);
@@ -171,6 +171,12 @@ hipError_t launch_w4a4_gemm_mid(const uint8_t* Xq, const float* a_scale, const f
                                 const uint8_t* Wq, const float* w_scale, const int32_t* border,
                                 int M, int N, int K, int g, uint16_t* Y, float out_scale,
                                 hipStream_t stream, WqLayout lay);
+// The tiled layout's alternative to the eight-wave weight stream, with its bits: 17 to 32
+// tokens at K = 8192, g <= 256.
+hipError_t launch_w4a4_gemm_mid_eighths(const uint8_t* Xq, const float* a_scale,
+                                        const float* s_group, const uint8_t* Wq,
+                                        const float* w_scale, int M, int N, int K, int g,
+                                        uint16_t* Y, float out_scale, hipStream_t stream);
 hipError_t launch_w4a4_gemm_mid_per_channel(const uint8_t* Xq, const float* a_scale,
                                             const uint8_t* Wq, const float* w_scale, int M, int N,
                                             int K, uint16_t* Y, float out_scale,

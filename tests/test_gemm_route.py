@@ -1,5 +1,8 @@
 """Which kernel a GEMM call takes, a host query: the calls below were measured on both
 kernels, and the one named is the faster (the times are beside the rule)."""
+import math
+import random
+
 import pytest
 
 import paper_2409_20361_amd as rrs
@@ -10,13 +13,14 @@ import paper_2409_20361_amd as rrs
     (16, 8192, 28672, 128, False, "stream"), (17, 8192, 28672, 128, False, "stream"),
     (32, 8192, 256, 64, False, "stream"), (24, 8192, 16384, 512, False, "stream"),
     (33, 8192, 28672, 128, False, "mid"), (24, 8192, 1024, 128, True, "stream"),
-    (20, 8192, 4096, 64, True, "stream"), (32, 8192, 4096, 64, True, "mid"),
-    (32, 8192, 28672, 512, True, "stream"), (32, 8192, 28672, 128, True, "mid"),
+    (20, 8192, 4096, 64, True, "stream"), (32, 8192, 4096, 64, True, "stream"),
+    (32, 8192, 28672, 512, True, "stream"), (33, 8192, 4096, 128, True, "mid"),
     # the few-token kernel above 16 tokens
     (17, 2048, 28672, 512, False, "decode"), (32, 4096, 12288, 256, False, "decode"),
     (32, 4096, 8192, 256, False, "mid"), (32, 4096, 12288, 128, False, "mid"),
     (33, 4096, 12288, 256, False, "mid"), (64, 16384, 12288, 256, False, "decode"),
-    (32, 16384, 20480, 512, True, "decode"), (48, 16384, 20480, 512, True, "mid"),
+    (32, 16384, 20480, 512, True, "decode"), (48, 16384, 10192, 512, True, "decode"),
+    (32, 2048, 20464, 256, False, "decode"), (32, 2048, 20400, 256, False, "mid"),
     (65, 16384, 12288, 256, False, "mid"), (64, 512, 28672, 64, True, "decode"),
     (32, 512, 28672, 64, True, "mid"),
 ])
@@ -47,6 +51,19 @@ def test_many_tokens(M, K, N, g, kind, tiled, path):
     assert rrs.gemm_path(M, N, K, g, flags, **forms) == path
     if path in ("main", "mid"):  # also the calls without scratch
         assert rrs.gemm_path(M, N, K, g, flags, scratch=False, **forms) == path
+
+
+def test_order_of_the_sum_does_not_depend_on_the_layout():
+    # one order each, but those of one entry share theirs
+    order = {"main": 0, "fp6_small": 0, "fp6_large": 0, "mid_eighths": "stream"}
+    rng = random.Random(3)
+    for _ in range(20000):
+        M = round(math.exp(rng.uniform(0, 9.1)))
+        K, N = 512 << rng.randrange(6), 16 * round(math.exp(rng.uniform(0, 7.5)))
+        g = rng.choice([64, 128, 256, 512])
+        kw = {"reorder": rng.random() < 0.5, "scratch": rng.random() < 0.7}
+        paths = [rrs.gemm_path(M, N, K, g, f, **kw) for f in (0, rrs.WEIGHT_TILED)]
+        assert order.get(paths[0], paths[0]) == order.get(paths[1], paths[1]), (M, N, K, g, kw)
 
 
 def test_other_forms_have_no_wide_few_token_kernel():

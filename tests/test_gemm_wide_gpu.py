@@ -17,9 +17,10 @@ torch = pytest.importorskip("torch")
     (17, 8192, 16, 64, False, "stream"), (32, 8192, 4112, 128, False, "stream"),
     (25, 8192, 272, 256, False, "stream"), (32, 8192, 48, 512, True, "stream"),
     (20, 8192, 80, 64, True, "stream"), (19, 8192, 10256, 512, True, "stream"),
-    (17, 2048, 12240, 256, False, "decode"), (32, 4096, 10192, 512, False, "decode"),
+    (17, 2048, 20432, 256, False, "decode"), (32, 4096, 10192, 512, False, "decode"),
     (33, 16384, 10192, 256, False, "decode"), (64, 16384, 10224, 512, False, "decode"),
-    (20, 16384, 10208, 512, True, "decode"), (33, 512, 10192, 64, True, "decode"),
+    (20, 16384, 10208, 512, True, "decode"), (64, 16384, 10192, 256, True, "decode"),
+    (32, 4096, 10256, 256, True, "decode"), (33, 512, 10192, 64, True, "decode"),
     (64, 512, 10208, 64, False, "decode"),
 ])
 def test_wide(M, K, N, g, tiled, path):
@@ -39,6 +40,27 @@ def test_wide(M, K, N, g, tiled, path):
     Y = rrs.w4a4_gemm(X, to_gpu(a), to_gpu(s), to_gpu(tile_wq(rows) if tiled else rows),
                       to_gpu(b), g, flags=fl)
     _check(to_np(Y), P, a, s, b, K, path)
+
+
+@pytest.mark.parametrize("M,N,g", [(17, 6144, 64), (32, 6160, 128), (25, 10224, 256),
+                                   (32, 10256, 64), (17, 12304, 128), (32, 28672, 256)])
+def test_eighths_of_k_are_the_streams_bits(M, N, g):
+    # With the tiled layout the mid-size kernel, in the order of the weight stream.
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_20361_amd as rrs
+    K = 8192
+    print(f"[case] eighths M={M} N={N} g={g}", flush=True)
+    assert rrs.gemm_path(M, N, K, g) == "stream"
+    assert rrs.gemm_path(M, N, K, g, rrs.WEIGHT_TILED) == "mid_eighths"
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, K), generator=gen, device="cuda").half()
+    X[:, ::97] *= 40
+    W = (0.02 * torch.randn((K, N), generator=gen, device="cuda")).half()
+    Xq, a, s = rrs.rotate_smooth_quant(X, g)
+    Y = [rrs.w4a4_gemm(Xq, a, s, *rrs.prepare_weight(W, None, f), g, flags=f)
+         for f in (0, rrs.WEIGHT_TILED)]
+    assert torch.equal(*Y)
 
 
 @pytest.mark.parametrize("M,K,N,paths", [
