@@ -515,6 +515,9 @@ size_t rrs_gemm_scratch_bytes(int M, int N, int K);
 const char* rrs_test_gemm_path(int M, int N, int K, int group_size, int flags, int scheme,
                                int reorder, int scratch);
 
+/* Test hook: blocks of 16 tokens per tile of the mid-size kernel (a host query). */
+int rrs_test_gemm_mid_token_blocks(int M, int N, int K, int tiled);
+
 /* rrs_w4a4_gemm_ex; with block_order rrs_w4a4_gemm_reorder; with s_group NULL
  * (then block_order too, and group_size ignored) rrs_w4a4_gemm_per_channel. */
 rrs_status rrs_w4a4_gemm_scratch(const void* Xq, const float* a_scale, const float* s_group,

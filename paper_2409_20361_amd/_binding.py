@@ -54,6 +54,7 @@ _SIGNATURES = {
     "rrs_linear_reorder": (ctypes.c_int32,
                            [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _sz, _vp]),
     "rrs_test_gemm_path": (ctypes.c_char_p, [_i, _i, _i, _i, _i, _i, _i, _i]),
+    "rrs_test_gemm_mid_token_blocks": (ctypes.c_int, [_i, _i, _i, _i]),
     "rrs_gemm_scratch_bytes": (_sz, [_i, _i, _i]),
     "rrs_w4a4_gemm_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i,
                                                _vp, _vp, _sz, _vp]),

@@ -459,6 +459,11 @@ const char* rrs_test_gemm_path(int M, int N, int K, int group_size, int flags, i
       {M, N, K, group_size, per_channel, reorder != 0, layout(flags).tiled}, scratch != 0));
 }
 
+int rrs_test_gemm_mid_token_blocks(int M, int N, int K, int tiled) {
+  if (!valid_m(M) || !valid_n(N) || !valid_k(K)) return 0;
+  return rrs::mid_token_blocks(M, N, K, tiled != 0);
+}
+
 rrs_status rrs_w4a4_gemm_ex(const void* Xq, const float* a_scale, const float* s_group,
                             const void* Wq, const float* w_scale, int M, int N, int K,
                             int group_size, int flags, void* Y, void* stream) {

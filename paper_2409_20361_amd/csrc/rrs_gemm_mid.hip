@@ -334,18 +334,22 @@ hipError_t launch(const uint8_t* Xq, const float* a_scale, const float* s_group,
 
 }  // namespace
 
-// Token blocks per tile: the largest tile that still gives 160 workgroups (a
-// little over half of the compute units; below that a smaller tile's second
-// pass over the weights, out of L2, costs less than the idle units). Measured,
-// row-major, 64 / 32 / 16 tokens per tile: 300 x 8192 x 1024 17.2 / 13.2 / 20.0
-// us (80 / 160 / 304 workgroups); 64 x 4096 x 4096 10.5 / 8.1 / 7.1 (64 / 128 /
-// 256); 32 x 16384 x 4096 - / 24.2 / 20.8 (64 / 128); 32 x 4096 x 12288 - / 8.4 /
-// 11.4 (192 / 384); 173 x 4096 x 4096 11.1 / 13.9 / 16.1 (192 / 384 / 704).
-int mid_token_blocks(int M, int N) {
-  const int tn = (N + BN - 1) / BN;
+// Token blocks per tile: the smaller tile while its workgroups fit one to a compute
+// unit (a second pass over the weights, out of L2, then costs less than idle units); past
+// 256 it takes a second round, and the larger tile is ahead although half of the units
+// idle. Measured, row-major, 16 / 32 / 64 tokens per tile (workgroups): 64 x 4096 x 4096
+// 7.1 / 8.1 / 10.5 us (256 / 128 / 64); 32 x 16384 x 4096 20.8 / 24.2 (128 / 64); 300 x 8192
+// x 1024 20.0 / 13.2 / 17.2 (304 / 160 / 80); 28 x 4096 x 9168, g = 256 13.4 / 10.0 (288 /
+// 144); 22 x 16384 x 9440, g = 64 72.9 / 42.4 (296 / 148); 61 x 8192 x 4688, g = 256 22.8 /
+// 15.9 / 20.7 (296 / 148 / 74); 49 x 8192 x 9104, g = 64 55.2 / 45.5 / 29.9 (572 / 286 /
+// 143). Up to K = 1024 with the tiled layout there is too little work for that below 160
+// large tiles (32 x 1024 x 8624 4.4 / 4.8; 58 x 1024 x 8944 with 32 or 64 tokens 4.8 / 5.2).
+int mid_token_blocks(int M, int N, int K, bool tiled) {
+  const long tn = (N + BN - 1) / BN;
+  auto wgs = [&](int rb) { return (M + 16 * rb - 1) / (16 * rb) * tn; };
   for (int rb = 4; rb > 1; rb /= 2) {
     if (M <= 8 * rb) continue;  // half of the tile would be idle
-    if ((M + 16 * rb - 1) / (16 * rb) * tn >= 160) return rb;
+    if (wgs(rb) >= 160 || (wgs(rb / 2) > 256 && !(tiled && K <= 1024))) return rb;
   }
   return 1;
 }
@@ -357,7 +361,7 @@ hipError_t launch_any(const uint8_t* Xq, const float* a_scale, const float* s_gr
                       const uint8_t* Wq, const float* w_scale, int M, int N, int K, int g,
                       uint16_t* Y, int32_t* P, float out_scale, hipStream_t stream,
                       const int32_t* border) {
-  const int rb = mid_token_blocks(M, N);
+  const int rb = mid_token_blocks(M, N, K, kTiled);
 #define RRS_MID(GS_, RB_)                                                                       \
   launch<GS_, RB_, mode, kGather, kTiled>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, P, \
                                           out_scale, stream, border)
@@ -413,7 +417,7 @@ hipError_t launch_w4a4_gemm_mid_eighths(const uint8_t* Xq, const float* a_scale,
                                         const float* w_scale, int M, int N, int K, int g,
                                         uint16_t* Y, float out_scale, hipStream_t stream) {
   if (K != 8192 || M > 32) return hipErrorInvalidValue;
-  const int rb = mid_token_blocks(M, N);
+  const int rb = mid_token_blocks(M, N, K, true);
 #define RRS_MID(GS_, RB_)                                                                     \
   launch<GS_, RB_, kSmooth, false, true, true>(Xq, a_scale, s_group, Wq, w_scale, M, N, K, Y, \
                                                nullptr, out_scale, stream, nullptr)

@@ -21,18 +21,22 @@ namespace {
 bool stream_wide(const GemmCall& c) { return c.M <= 32 && c.K == 8192; }
 bool mid_eighths(const GemmCall& c) { return c.tiled && c.N >= 6144 && c.g <= 256; }
 
-// 17 to 64 tokens, long groups, from the width on where the mid-size kernel's tiles
-// are 32 tokens and more (160 tiles of columns): a wave of the few-token kernel reads
-// a group of a row at once, 128 or 256 bytes, and the mid-size kernel 64. Few-token /
-// mid, row-major, g = 256, N = 12288: 32 x 4096 9.7 / 10.5, 32 x 16384 28.4 / 34.7, 64 x
-// 16384 38.0 / 42.7 (tiled between 5 % ahead and 13 % behind). With two groups of 64 per
-// wave (K = 512) the mid-size kernel's prologue and sum are all there is: 64 x 512 x 20480
-// 9.1 / 11.4. At K = 2048 the line is where the mean of both layouts turns.
+// 17 to 64 tokens, long groups, from 160 tiles of columns on (129 at K = 512 and 16384, where
+// the mid-size kernel's tiles grow; there not from 33 tokens on with g = 256, which the mid-size
+// kernel multiplies faster with the tiled layout: 39 x 16384 x 9040 33.9 / 30.2): a wave of the
+// few-token kernel reads a group of a row at once, 128 or 256 bytes, and the mid-size kernel
+// 64. Few-token / mid, row-major, g = 256, N = 12288: 32 x 4096 9.7 / 10.5, 32 x 16384 28.4 /
+// 34.7, 64 x 16384 38.0 / 42.7; g = 512, 29 x 16384 x 9040 27.3 / 31.1, 46 x 16384 x 9968 34.6
+// / 37.4 (tiled between 5 % ahead and 13 % behind). With two groups of 64 per wave (K = 512)
+// the mid-size kernel's prologue and sum are all there is: 64 x 512 x 20480 9.1 / 11.4, 49 x
+// 512 x 9664 6.3 / 7.1. At K = 2048 the line is where the mean of both layouts turns.
 bool decode_wide(const GemmCall& c) {
   const int columns = (c.N + 63) / 64;
-  if (!decode_wide_fits(c.M, c.K, c.g) || columns < 160) return false;
+  if (!decode_wide_fits(c.M, c.K, c.g)) return false;
+  if (columns <= 128) return false;
   if (c.K == 512) return c.g == 64;
-  if (c.K == 16384) return true;
+  if (c.K == 16384) return columns >= 160 || c.M <= 32 || c.g == 512;
+  if (columns < 160) return false;
   if (c.M > 32) return false;
   return c.K == 4096 || (c.K == 2048 && columns >= (c.g == 512 ? 192 : 320));
 }
@@ -84,7 +88,7 @@ double fit_us(const Fit& f, const GemmCall& c, int bm, int cap) {
 // the sum; row-major weights cost more the fewer tokens share them, gathered ones once
 // the caches no longer hold them.
 double mid_us(const GemmCall& c) {
-  const int rb = mid_token_blocks(c.M, c.N);
+  const int rb = mid_token_blocks(c.M, c.N, c.K, c.tiled);
   const int i = rb == 4 ? 0 : rb == 2 ? 1 : 2;
   constexpr double kTile[3] = {0.313, 0.175, 0.145}, kRow[3] = {0.336, 0.564, 0.777};
   const long per = ((long)ceil_div(c.M, 16 * rb) * ceil_div(c.N, 64) + 7) / 8;
@@ -124,8 +128,13 @@ GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
   // tiles, and from K = 4096 the caches no longer hold them: 547 x 8192 x 23696, g = 256,
   // 328 us, main 207; 548 x 4096 x 22016, g = 512, 142 / 104; 1020 x 4096 x 12288, g = 256,
   // 80 / 78. (g = 64, where the main kernel is slowest, stays: 1867 x 8192 x 8512 231 / 278.)
-  if (p == GemmPath::kFp6Small && c.reorder && !c.tiled && c.K >= 4096 && c.g >= 128)
-    return GemmPath::kMain;
+  // So does a single row of large tiles from K = 8192, each of which gathers weights of its
+  // own: 134 x 8192 x 18400, g = 128, 82.4 / 78.0; 141 x 16384 x 17472 172 / 158 (187 x 4096
+  // x 17040 41.3 / 42.7).
+  const int gathered = p == GemmPath::kFp6Small                  ? 4096
+                       : p == GemmPath::kFp6Large && c.M <= 256 ? 8192
+                                                                : 0;
+  if (gathered && c.K >= gathered && c.reorder && !c.tiled && c.g >= 128) return GemmPath::kMain;
   const bool same_order =
       c.per_channel || p == GemmPath::kFp6Small || p == GemmPath::kFp6Large;
   const bool main = same_order ? path_us(GemmPath::kMain, c) < path_us(p, c)

@@ -166,7 +166,7 @@ hipError_t launch_w4a4_gemm_decode_partials(const uint8_t* Xq, const uint8_t* Wq
 // 17 to a few hundred tokens (rrs_gemm_mid.hip): small tiles whose waves split
 // K. mid_kernel_fits says where it may beat the main kernel; it takes any M.
 bool mid_kernel_fits(int M, int N);
-int mid_token_blocks(int M, int N);  // blocks of 16 tokens per tile
+int mid_token_blocks(int M, int N, int K, bool tiled);  // blocks of 16 tokens per tile
 hipError_t launch_w4a4_gemm_mid(const uint8_t* Xq, const float* a_scale, const float* s_group,
                                 const uint8_t* Wq, const float* w_scale, const int32_t* border,
                                 int M, int N, int K, int g, uint16_t* Y, float out_scale,

@@ -21,7 +21,10 @@ import paper_2409_20361_amd as rrs
     (33, 4096, 12288, 256, False, "mid"), (64, 16384, 12288, 256, False, "decode"),
     (32, 16384, 20480, 512, True, "decode"), (48, 16384, 10192, 512, True, "decode"),
     (32, 2048, 20464, 256, False, "decode"), (32, 2048, 20400, 256, False, "mid"),
-    (65, 16384, 12288, 256, False, "mid"), (64, 512, 28672, 64, True, "decode"),
+    (65, 16384, 12288, 256, False, "mid"), (32, 16384, 8208, 256, False, "decode"),
+    (32, 16384, 8192, 512, False, "mid"), (64, 16384, 8208, 512, True, "decode"),
+    (33, 16384, 10176, 256, False, "mid"), (64, 512, 28672, 64, True, "decode"),
+    (33, 512, 8208, 64, False, "decode"), (33, 512, 8192, 64, False, "mid"),
     (32, 512, 28672, 64, True, "mid"),
 ])
 def test_few_tokens(M, K, N, g, tiled, path):
@@ -38,7 +41,10 @@ def test_few_tokens(M, K, N, g, tiled, path):
     (5346, 2048, 784, 64, "per_channel", False, "main"),
     (8192, 2048, 1024, 512, "reorder", False, "main"),
     (547, 8192, 23696, 256, "reorder", False, "main"), (89, 512, 22016, 512, None, False, "main"),
+    (134, 8192, 18400, 128, "reorder", False, "main"),
+    (134, 8192, 18400, 128, "reorder", True, "fp6_large"),
     # and the others where they are ahead
+    (187, 4096, 17040, 128, "reorder", False, "fp6_large"),
     (173, 4096, 4096, 128, None, False, "mid"), (512, 8192, 8192, 128, None, False, "fp6_teams"),
     (1024, 4096, 12288, 128, "per_channel", False, "fp6_small"),
     (1500, 4096, 12288, 128, "reorder", False, "fp6_tail"),
@@ -70,6 +76,21 @@ def test_other_forms_have_no_wide_few_token_kernel():
     for M, K, N, g in ((24, 8192, 1024, 128), (32, 16384, 12288, 512), (48, 512, 28672, 64)):
         for kind in ("reorder", "per_channel"):
             assert rrs.gemm_path(M, N, K, g, **{kind: True}, scratch=False) in ("mid", "main")
+
+
+@pytest.mark.parametrize("M,K,N,tiled,blocks", [
+    # the larger tile from where the smaller one takes more than 256 workgroups
+    (22, 16384, 8192, False, 1), (22, 16384, 8208, False, 2), (28, 4096, 9168, False, 2),
+    (61, 8192, 4096, False, 1), (61, 8192, 4112, False, 2), (49, 8192, 8192, False, 2),
+    (49, 8192, 8208, False, 4), (49, 8192, 8208, True, 4), (16, 4096, 28672, False, 1),
+    (64, 4096, 4096, False, 1), (32, 16384, 4096, False, 1), (173, 4096, 4096, False, 4),
+    (300, 8192, 1024, False, 2), (32, 4096, 12288, False, 2), (33, 4096, 28672, False, 4),
+    # tiled and K up to 1024: from 160 of the larger
+    (32, 1024, 8624, True, 1), (32, 1024, 10192, True, 2), (58, 512, 8944, True, 2),
+    (32, 2048, 8624, True, 2),
+])
+def test_mid_size_tile(M, K, N, tiled, blocks):
+    assert rrs.lib().rrs_test_gemm_mid_token_blocks(M, N, K, int(tiled)) == blocks
 
 
 def test_invalid():
