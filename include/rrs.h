@@ -494,9 +494,11 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
  * token codes can first be written out in the matrix instruction's operand
  * order (0.82 bytes per code). The functions below are the ones of the same
  * names without "_scratch" plus a scratch buffer for that: same arguments,
- * checks and results (Y up to the order of its f32 sum over the groups: the same
- * bits where one team of waves takes all of K, a float16 step here and there in
- * mid-size calls where two share it). scratch may be NULL or smaller than
+ * checks and results, Y up to the order of its f32 sum over the groups: the same
+ * bits where rrs_test_gemm_path names the same kernel with and without scratch, or two of
+ * "main", "fp6_small" and "fp6_large", else a float16 step here and there. ("fp6_teams" adds
+ * the sums of two halves of K, "fp6_tail" does so in the tiles of its last round only, so
+ * rows of one call may differ in the order. The per-channel scheme's sum is exact.) scratch may be NULL or smaller than
  * rrs_gemm_scratch_bytes: the call then runs as the plain function does. It
  * must be 16-byte aligned, its contents before and after are undefined, and
  * calls that may overlap need a scratch buffer each.
@@ -506,6 +508,11 @@ rrs_status rrs_linear_reorder(const void* X, const void* Wq, const float* w_scal
 /* Scratch bytes with which the GEMM of this shape runs faster; 0 when none are
  * used (few tokens, or invalid arguments). Any group size and flags. */
 size_t rrs_gemm_scratch_bytes(int M, int N, int K);
+
+/* The same for one call: 0 where that call runs as the plain function does in any case.
+ * scheme, reorder: as in rrs_test_gemm_path below. */
+size_t rrs_gemm_scratch_bytes_ex(int M, int N, int K, int group_size, int flags, int scheme,
+                                 int reorder);
 
 /* Test hook: the name of the kernel a GEMM call takes, a host query ("stream",
  * "stream_gather", "decode", "decode_gather", "mid", "mid_eighths", "main", "fp6_teams", "fp6_small",

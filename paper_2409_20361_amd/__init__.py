@@ -22,6 +22,7 @@ from ._binding import (  # noqa: F401
     WEIGHT_TILED,
     RRSError,
     gemm_path,
+    gemm_scratch_bytes,
     lib,
     lib_path,
     linear,
@@ -49,7 +50,7 @@ from ._binding import (  # noqa: F401
 
 __all__ = [
     "REORDER_BLOCK", "SCHEME_PER_CHANNEL", "SCHEME_RUNTIME_SMOOTH", "SCHEME_SUB_CHANNEL",
-    "SKIP_ROTATION", "SKIP_SMOOTHING", "WEIGHT_TILED", "RRSError", "gemm_path", "lib", "lib_path", "linear", "linear_noalloc", "linear_reorder",
+    "SKIP_ROTATION", "SKIP_SMOOTHING", "WEIGHT_TILED", "RRSError", "gemm_path", "gemm_scratch_bytes", "lib", "lib_path", "linear", "linear_noalloc", "linear_reorder",
     "linear_reorder_workspace_bytes", "linear_workspace_bytes",
     "prepare_weight", "prepare_weight_sub_channel", "quant_rows_wait_hook",
     "quant_reorder_wait_hook",

@@ -56,6 +56,7 @@ _SIGNATURES = {
     "rrs_test_gemm_path": (ctypes.c_char_p, [_i, _i, _i, _i, _i, _i, _i, _i]),
     "rrs_test_gemm_mid_token_blocks": (ctypes.c_int, [_i, _i, _i, _i]),
     "rrs_gemm_scratch_bytes": (_sz, [_i, _i, _i]),
+    "rrs_gemm_scratch_bytes_ex": (_sz, [_i, _i, _i, _i, _i, _i, _i]),
     "rrs_w4a4_gemm_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i,
                                                _vp, _vp, _sz, _vp]),
     "rrs_linear_scratch": (ctypes.c_int32, [_vp, _vp, _vp, _i, _i, _i, _i, _vp, _i, _vp, _vp, _sz,
@@ -154,14 +155,46 @@ def _dev(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Tuple[int, ...])
     return t.data_ptr()
 
 
-def _gemm_scratch(M: int, N: int, K: int, device: torch.device):
-    """Scratch of the many-token GEMM as (tensor, pointer, bytes), from torch's caching
-    allocator on the current stream (which the call's launches use too, so the memory is
-    not handed out again before they ran); (None, None, 0) for few tokens."""
-    nbytes = lib().rrs_gemm_scratch_bytes(M, N, K) if M > 16 else 0
+def gemm_scratch_bytes(M: int, N: int, K: int) -> int:
+    """Bytes of `scratch` that every GEMM of this shape can use (0: none is used)."""
+    return lib().rrs_gemm_scratch_bytes(M, N, K)
+
+
+def _outlives_capture(t: torch.Tensor) -> bool:
+    """Whether t lies in a private pool of the caching allocator, as under torch.cuda.graph:
+    only that keeps the memory for the graph's replays after t is freed."""
+    p = t.data_ptr()
+    for seg in torch.cuda.memory_snapshot():
+        if seg["address"] <= p < seg["address"] + seg["total_size"]:
+            return tuple(seg.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
+def _gemm_scratch(scratch: Optional[torch.Tensor], M: int, N: int, K: int, g: int, flags: int,
+                  device: torch.device, reorder: bool = False, per_channel: bool = False):
+    """Scratch of the many-token GEMM as (tensor, pointer, bytes): the caller's; else, where the
+    call uses any, from torch's caching allocator on the current stream (which the call's
+    launches use too, so the memory is not handed out again before they ran). Without
+    scratch, (None, None, 0), the call still runs: for few tokens, when the memory is not
+    to be had, and under a capture that torch does not manage (the graph would replay into memory
+    that has been handed out again)."""
+    if scratch is not None:
+        if scratch.device != device or not scratch.is_contiguous():
+            raise ValueError(f"scratch must be contiguous and on {device}")
+        return scratch, scratch.data_ptr(), scratch.numel() * scratch.element_size()
+    nbytes = 0
+    if M > 16:
+        nbytes = lib().rrs_gemm_scratch_bytes_ex(
+            M, N, K, g, flags, SCHEME_PER_CHANNEL if per_channel else SCHEME_RUNTIME_SMOOTH,
+            reorder)
     if nbytes == 0:
         return None, None, 0
-    t = torch.empty((nbytes,), dtype=torch.uint8, device=device)
+    try:
+        t = torch.empty((nbytes,), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None, None, 0
+    if torch.cuda.is_current_stream_capturing() and not _outlives_capture(t):
+        return None, None, 0
     return t, t.data_ptr(), nbytes
 
 
@@ -210,8 +243,14 @@ def rotate_smooth_quant(X: torch.Tensor, g: int, perm: Optional[torch.Tensor] = 
 
 def w4a4_gemm(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Tensor,
               Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
-              out: Optional[torch.Tensor] = None, flags: int = 0) -> torch.Tensor:
-    """Y = fp16(a_i w_n / K * sum_b s_b P_b) (M x N; no 1/K with SKIP_ROTATION)."""
+              out: Optional[torch.Tensor] = None, flags: int = 0,
+              scratch: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Y = fp16(a_i w_n / K * sum_b s_b P_b) (M x N; no 1/K with SKIP_ROTATION).
+
+    With many tokens the GEMM spreads the token codes into scratch memory first: `scratch`
+    (gemm_scratch_bytes(M, N, K) bytes) where it is given, else a tensor that lives for the
+    call. With a smaller one (or where none is to be had) it runs without, slower; Y is
+    then the same up to the order of the float32 sum over the groups."""
     M, Kh = Xq.shape
     K = 2 * Kh
     N = Wq.shape[0]
@@ -220,7 +259,7 @@ def w4a4_gemm(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Tensor,
             _dev(Wq, "Wq", torch.uint8, (N, Kh)), _dev(w_scale, "w_scale", torch.float32, (N,)))
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    keep, sp, sb = _gemm_scratch(scratch, M, N, K, g, flags, Xq.device)
     _check(lib().rrs_w4a4_gemm_scratch(*args, None, M, N, K, g, flags, yp, sp, sb,
                                        _stream(Xq.device)), "rrs_w4a4_gemm")
     return Y
@@ -228,8 +267,9 @@ def w4a4_gemm(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Tensor,
 
 def linear(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
            perm: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
-           out: Optional[torch.Tensor] = None, flags: int = 0) -> torch.Tensor:
-    """One RRS linear layer: X M x K fp16 -> Y M x N fp16."""
+           out: Optional[torch.Tensor] = None, flags: int = 0,
+           scratch: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """One RRS linear layer: X M x K fp16 -> Y M x N fp16 (scratch: as in w4a4_gemm)."""
     M, K = X.shape
     N = Wq.shape[0]
     xp = _dev(X, "X", torch.float16, (M, K))
@@ -240,7 +280,7 @@ def linear(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    keep, sp, sb = _gemm_scratch(M, N, K, X.device)
+    keep, sp, sb = _gemm_scratch(scratch, M, N, K, g, flags, X.device)
     _check(lib().rrs_linear_scratch(xp, wqp, wsp, M, N, K, g, _perm_ptr(perm, K), flags, yp,
                                     workspace.data_ptr(),
                                     workspace.numel() * workspace.element_size(), sp, sb,
@@ -253,7 +293,10 @@ def linear_noalloc(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: 
                    ) -> torch.Tensor:
     """rrs_linear with the library-held scratch instead of a workspace: the C call
     allocates nothing (for graph capture and serving loops). Only Y is
-    allocated here, and only when `out` is not given."""
+    allocated here, and only when `out` is not given. Its GEMM has no scratch: Y is that of
+    `linear` bit for bit where gemm_path names the same kernel with and without scratch, or
+    two of "main", "fp6_small" and "fp6_large", and up to the order of the float32 sum over the groups
+    elsewhere (a float16 step here and there)."""
     M, K = X.shape
     N = Wq.shape[0]
     xp = _dev(X, "X", torch.float16, (M, K))
@@ -390,8 +433,10 @@ def w4a4_gemm_scheme(scheme: int, Xq: torch.Tensor, x_scale: torch.Tensor,
 
 def w4a4_gemm_per_channel(Xq: torch.Tensor, a_scale: torch.Tensor, Wq: torch.Tensor,
                           w_scale: torch.Tensor, flags: int = 0,
-                          out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """Per-channel A4W4 on the tuned main loop: Y = fp16(a_i w_n / K * sum_j q q)."""
+                          out: Optional[torch.Tensor] = None,
+                          scratch: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Per-channel A4W4 on the tuned main loop: Y = fp16(a_i w_n / K * sum_j q q) (scratch: as
+    in w4a4_gemm; Y is the same bits with and without)."""
     M, Kh = Xq.shape
     N = Wq.shape[0]
     K = 2 * Kh
@@ -402,7 +447,7 @@ def w4a4_gemm_per_channel(Xq: torch.Tensor, a_scale: torch.Tensor, Wq: torch.Ten
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(out, "Y", torch.float16, (M, N))
-    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    keep, sp, sb = _gemm_scratch(scratch, M, N, K, 0, flags, Xq.device, per_channel=True)
     _check(lib().rrs_w4a4_gemm_scratch(xq, ap, None, wq, wp, None, M, N, K, 0, flags, yp, sp, sb,
                                        _stream(Xq.device)), "rrs_w4a4_gemm_per_channel")
     return out
@@ -440,8 +485,10 @@ def rotate_smooth_quant_reorder(X: torch.Tensor, g: int, workspace: Optional[tor
 
 def w4a4_gemm_reorder(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Tensor,
                       Wq: torch.Tensor, w_scale: torch.Tensor, block_order: torch.Tensor, g: int,
-                      out: Optional[torch.Tensor] = None, flags: int = 0) -> torch.Tensor:
-    """GEMM pairing position block p of Xq with block block_order[p] of every Wq row."""
+                      out: Optional[torch.Tensor] = None, flags: int = 0,
+                      scratch: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """GEMM pairing position block p of Xq with block block_order[p] of every Wq row (scratch:
+    as in w4a4_gemm)."""
     M, Kh = Xq.shape
     K = 2 * Kh
     N = Wq.shape[0]
@@ -451,7 +498,7 @@ def w4a4_gemm_reorder(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Te
             _dev(block_order, "block_order", torch.int32, (K // REORDER_BLOCK,)))
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=Xq.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    keep, sp, sb = _gemm_scratch(M, N, K, Xq.device)
+    keep, sp, sb = _gemm_scratch(scratch, M, N, K, g, flags, Xq.device, reorder=True)
     _check(lib().rrs_w4a4_gemm_scratch(*args, M, N, K, g, flags, yp, sp, sb, _stream(Xq.device)),
            "rrs_w4a4_gemm_reorder")
     return Y
@@ -459,8 +506,9 @@ def w4a4_gemm_reorder(Xq: torch.Tensor, a_scale: torch.Tensor, s_group: torch.Te
 
 def linear_reorder(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: int,
                    workspace: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
-                   flags: int = 0) -> torch.Tensor:
-    """One RRS linear layer with the runtime reorder: X M x K fp16 -> Y M x N fp16."""
+                   flags: int = 0, scratch: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """One RRS linear layer with the runtime reorder: X M x K fp16 -> Y M x N fp16 (scratch: as
+    in w4a4_gemm)."""
     M, K = X.shape
     N = Wq.shape[0]
     xp = _dev(X, "X", torch.float16, (M, K))
@@ -471,7 +519,7 @@ def linear_reorder(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: 
         workspace = torch.zeros((max(nbytes, 1),), dtype=torch.uint8, device=X.device)
     Y = out if out is not None else torch.empty((M, N), dtype=torch.float16, device=X.device)
     yp = _dev(Y, "Y", torch.float16, (M, N))
-    keep, sp, sb = _gemm_scratch(M, N, K, X.device)
+    keep, sp, sb = _gemm_scratch(scratch, M, N, K, g, flags, X.device, reorder=True)
     _check(lib().rrs_linear_reorder_scratch(xp, wqp, wsp, M, N, K, g, flags, yp,
                                             workspace.data_ptr(),
                                             workspace.numel() * workspace.element_size(), sp, sb,

@@ -15,7 +15,7 @@
 
 namespace {
 
-constexpr int kVersion = 601;  // 0.6.1: one-launch runtime-reorder quantizer for up to 16 tokens
+constexpr int kVersion = 602;  // 0.6.2: GEMM on scratch memory
 constexpr int kMaxDevices = 64;
 
 bool is_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -440,6 +440,16 @@ hipError_t run_gemm(const void* Xq, const float* a, const float* s, const void* 
   return rrs::launch_w4a4_gemm(xq, a, s, wq, w, M, N, K, g, y, os, st, lay);
 }
 
+// A call of the host queries, checked as the call itself would be.
+bool gemm_call(int M, int N, int K, int g, int flags, int scheme, int reorder, rrs::GemmCall* c) {
+  const bool per_channel = scheme == RRS_SCHEME_PER_CHANNEL;
+  if (!valid_m(M) || !valid_n(N) || !valid_k(K) || (per_channel && reorder) ||
+      (!per_channel && !valid_group(K, g)))
+    return false;
+  *c = {M, N, K, g, per_channel, reorder != 0, layout(flags).tiled};
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -449,14 +459,18 @@ size_t rrs_gemm_scratch_bytes(int M, int N, int K) {
   return rrs::fp6_scratch_bytes(M, N, K);
 }
 
+size_t rrs_gemm_scratch_bytes_ex(int M, int N, int K, int group_size, int flags, int scheme,
+                                 int reorder) {
+  rrs::GemmCall c;
+  if (!gemm_call(M, N, K, group_size, flags, scheme, reorder, &c)) return 0;
+  return rrs::on_scratch(rrs::gemm_path(c, true)) ? rrs::fp6_scratch_bytes(M, N, K) : 0;
+}
+
 const char* rrs_test_gemm_path(int M, int N, int K, int group_size, int flags, int scheme,
                                int reorder, int scratch) {
-  const bool per_channel = scheme == RRS_SCHEME_PER_CHANNEL;
-  if (!valid_m(M) || !valid_n(N) || !valid_k(K) || (per_channel && reorder) ||
-      (!per_channel && !valid_group(K, group_size)))
-    return "";
-  return rrs::gemm_path_name(rrs::gemm_path(
-      {M, N, K, group_size, per_channel, reorder != 0, layout(flags).tiled}, scratch != 0));
+  rrs::GemmCall c;
+  if (!gemm_call(M, N, K, group_size, flags, scheme, reorder, &c)) return "";
+  return rrs::gemm_path_name(rrs::gemm_path(c, scratch != 0));
 }
 
 int rrs_test_gemm_mid_token_blocks(int M, int N, int K, int tiled) {

@@ -130,3 +130,71 @@ def test_scratch_buffer_is_optional():
     assert bool((buf[need:] == 0xA5).all())             # nothing written past it
     assert call(buf.data_ptr() + 8, need)[0] == -4      # not 16-byte aligned
     assert lib.rrs_gemm_scratch_bytes(16, N, K) == 0    # few tokens use none
+
+
+def test_scratch_of_the_python_calls(monkeypatch):
+    # The caller's buffer is the one that is used; without it one of the call's own, or none
+    # where the memory is not to be had. One team of waves: Y is the same bits in each case.
+    import paper_2409_20361_amd as rrs
+    M, K, N, g = 257, 512, 19696, 256
+    for form in ({}, {"reorder": True}, {"per_channel": True}):
+        assert rrs.gemm_path(M, N, K, g, **form) == "fp6_small"
+        assert rrs.gemm_path(M, N, K, g, scratch=False, **form) == "main"
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((M, K), device="cuda", generator=gen).half()
+    Wq, w = rrs.prepare_weight((0.02 * torch.randn((K, N), device="cuda", generator=gen)).half())
+    ws = torch.zeros(rrs.linear_reorder_workspace_bytes(M, K, g), dtype=torch.uint8, device="cuda")
+    need = rrs.gemm_scratch_bytes(M, N, K)
+    Xq, a, s = rrs.rotate_smooth_quant(X, g)
+    order = torch.arange(K // 32, dtype=torch.int32, device="cuda").flip(0).contiguous()
+    calls = [lambda **k: rrs.linear(X, Wq, w, g, workspace=ws, **k),
+             lambda **k: rrs.linear_reorder(X, Wq, w, g, workspace=ws, **k),
+             lambda **k: rrs.w4a4_gemm(Xq, a, s, Wq, w, g, **k),
+             lambda **k: rrs.w4a4_gemm_reorder(Xq, a, s, Wq, w, order, g, **k),
+             lambda **k: rrs.w4a4_gemm_per_channel(Xq, a, Wq, w, **k)]
+    empty = torch.empty
+    for i, call in enumerate(calls):
+        print(f"[case] scratch of call {i}", flush=True)
+        Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        ref = call(out=torch.empty_like(Y))
+        sizes = []
+
+        def counted(size, **k):
+            sizes.append(size)
+            return empty(size, **k)
+
+        def refused(size, **k):
+            raise torch.OutOfMemoryError("full card")
+
+        buf = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+        with monkeypatch.context() as m:                # given: nothing is allocated
+            m.setattr(torch, "empty", counted)
+            call(out=Y, scratch=buf)
+        torch.cuda.synchronize()
+        assert not sizes and torch.equal(Y, ref) and not bool((buf == 0xA5).all())
+        small = torch.full((need - 16,), 0xA5, dtype=torch.uint8, device="cuda")
+        assert torch.equal(call(out=Y, scratch=small), ref) and bool((small == 0xA5).all())
+        with monkeypatch.context() as m:                # a full card: the plain path
+            m.setattr(torch, "empty", refused)
+            call(out=Y.zero_())
+        assert torch.equal(Y, ref)
+        with pytest.raises(ValueError):
+            call(out=Y, scratch=torch.empty(need, dtype=torch.uint8))
+
+
+def test_scratch_under_capture(monkeypatch):
+    import paper_2409_20361_amd as rrs
+    from paper_2409_20361_amd import _binding
+    M, K, N, g = 257, 512, 19696, 256
+    dev = torch.device("cuda", torch.cuda.current_device())
+    need = rrs.gemm_scratch_bytes(M, N, K)
+    got = lambda: _binding._gemm_scratch(None, M, N, K, g, 0, dev)  # noqa: E731
+    assert got()[2] == need
+    with monkeypatch.context() as m:    # capturing, but the allocator has no pool for it
+        m.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+        assert got() == (None, None, 0)
+    x = torch.zeros(8, device=dev)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):       # torch's own capture
+        x.add_(1)
+        assert got()[2] == need

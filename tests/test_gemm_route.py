@@ -78,6 +78,24 @@ def test_other_forms_have_no_wide_few_token_kernel():
             assert rrs.gemm_path(M, N, K, g, **{kind: True}, scratch=False) in ("mid", "main")
 
 
+def test_scratch_of_a_call():
+    # The shape's bytes where this call takes a kernel on scratch, 0 where it does not.
+    rng, seen = random.Random(5), {}
+    for _ in range(4000):
+        M = round(math.exp(rng.uniform(0, 9.1)))
+        K, N = 512 << rng.randrange(6), 16 * round(math.exp(rng.uniform(0, 7.5)))
+        g, f = rng.choice([64, 128, 256, 512]), rng.choice([0, rrs.WEIGHT_TILED])
+        kind = rng.choice([None, "reorder", "per_channel"])
+        path = rrs.gemm_path(M, N, K, g, f, **({kind: True} if kind else {}))
+        nbytes = rrs.lib().rrs_gemm_scratch_bytes_ex(M, N, K, g, f, int(kind != "per_channel"),
+                                                     int(kind == "reorder"))
+        assert nbytes == (rrs.gemm_scratch_bytes(M, N, K) if path.startswith("fp6") else 0)
+        seen[path.startswith("fp6")] = seen.get(path.startswith("fp6"), 0) + 1
+    assert len(seen) == 2
+    assert rrs.lib().rrs_gemm_scratch_bytes_ex(520, 4112, 2048, 0, 0, 0, 0) == 0  # mid-size
+    assert rrs.lib().rrs_gemm_scratch_bytes_ex(520, 4112, 2048, 96, 0, 1, 0) == 0  # no such group
+
+
 @pytest.mark.parametrize("M,K,N,tiled,blocks", [
     # the larger tile from where the smaller one takes more than 256 workgroups
     (22, 16384, 8192, False, 1), (22, 16384, 8208, False, 2), (28, 4096, 9168, False, 2),

@@ -31,10 +31,12 @@ def _rrs():
     (8, 8192, 256, 128, False),    # one-launch few-token quantizer, few-token GEMM
     (1, 4096, 4112, 128, False),   # the whole layer in one launch (one token)
     (2, 8192, 512, 256, False),    # the whole layer in one launch (two tokens)
-    (40, 8192, 4112, 128, False),  # per-row quantizer (shared reads), few-token GEMM
-    (300, 4096, 384, 128, False),  # two-launch quantizer, main GEMM
-    (16, 2048, 128, 64, True),     # reorder: three quantizer launches, few-token gather
-    (260, 1024, 256, 256, True),   # reorder: main-kernel gather
+    (40, 8192, 4112, 128, False),  # per-row quantizer (shared reads), mid-size GEMM
+    (300, 4096, 384, 128, False),  # two-launch quantizer, mid-size GEMM
+    (16, 2048, 128, 64, True),     # reorder: one-launch quantizer, few-token gather
+    (260, 1024, 256, 256, True),   # reorder: mid-size gather
+    (520, 2048, 4112, 128, False),  # on scratch memory of the call: two teams
+    (257, 512, 19696, 256, True),   # reorder, on scratch memory: 128 x 128 tiles
 ])
 def test_graph_replay_matches_eager(M, K, N, g, reorder):
     rrs = _rrs()
