@@ -311,7 +311,8 @@ def linear_noalloc(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, g: 
 
 def w4a4_gemm_partials(Xq: torch.Tensor, Wq: torch.Tensor, g: int) -> torch.Tensor:
     """Exact int32 group partials P[b, i, n] (test hook) from the kernel that
-    rrs_w4a4_gemm runs for this shape with row-major Wq."""
+    rrs_w4a4_gemm runs for this shape with row-major Wq and no scratch (the 6-bit
+    kernels have no such hook; w4a4_gemm of this module may take them)."""
     M, Kh = Xq.shape
     K = 2 * Kh
     N = Wq.shape[0]

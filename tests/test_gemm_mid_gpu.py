@@ -62,6 +62,8 @@ CASES = [
     (31, 2048, 2576, 256, True), (32, 16384, 64, 128, False), (65, 4096, 80, 64, True),
     (130, 1024, 5136, 128, False), (63, 2048, 10256, 64, False), (200, 2048, 2064, 512, True),
     (49, 8192, 176, 256, False),
+    # the first columns where the larger tile is taken: 32 and 64 tokens
+    (20, 1024, 8208, 64, False), (33, 2048, 8208, 128, True), (61, 4096, 4112, 512, False),
 ]
 
 
@@ -69,13 +71,15 @@ CASES = [
 def test_mid_gemm(M, K, N, g, tiled):
     import paper_2409_20361_amd as rrs
     print(f"[case] mid GEMM M={M} K={K} N={N} g={g} tiled={tiled}", flush=True)
+    fl = rrs.WEIGHT_TILED if tiled else 0
+    for form in ({}, {"reorder": True}, {"per_channel": True}):
+        assert rrs.gemm_path(M, N, K, g, fl, **form) == "mid"
     qx, qw, a, s, b = _case(M, K, N, g, M + K)
     P = _partials(qx, qw, g)
     X, A, S, B = to_gpu(_pack(qx)), to_gpu(a), to_gpu(s), to_gpu(b)
     rows = _pack(qw)
     assert np.array_equal(to_np(rrs.w4a4_gemm_partials(X, to_gpu(rows), g)), P)
     W = to_gpu(tile_wq(rows) if tiled else rows)
-    fl = rrs.WEIGHT_TILED if tiled else 0
     _check(to_np(rrs.w4a4_gemm(X, A, S, W, B, g, flags=fl)), P, a, s, b, K, "plain")
     # per-channel: one exact sum over K
     y = to_np(rrs.w4a4_gemm_per_channel(X, A, W, B, flags=fl))

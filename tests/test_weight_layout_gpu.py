@@ -78,7 +78,9 @@ def test_tiled_sub_channel_prepare():
 @pytest.mark.parametrize("M,K,N,g", [
     (1, 8192, 256, 128), (8, 4096, 512, 64), (16, 2048, 128, 512), (24, 4096, 512, 256),
     (64, 2048, 384, 512), (65, 4096, 512, 128), (300, 1024, 640, 128),
-    (8, 4096, 208, 128), (40, 2048, 336, 64)])
+    (8, 4096, 208, 128), (40, 2048, 336, 64),
+    # a kernel each: 6-bit tiles of 128 x 128 / the main kernel; the weight stream / eighths of K
+    (257, 512, 9968, 128), (24, 8192, 6160, 64)])
 def test_gemm_and_linear_agree_across_layouts(M, K, N, g):
     rrs = _rrs()
     print(f"[case] layouts gemm/linear M={M} K={K} N={N} g={g}", flush=True)
