@@ -561,23 +561,6 @@ __device__ __forceinline__ void gemm_fp6_tile(
     store(std::false_type{});
 }
 
-template <int GS, int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
-__global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
-    const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
-    const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
-    const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
-    float out_scale, const int32_t* __restrict__ border) {
-  __shared__ __attribute__((aligned(16))) uint8_t stages[KS * 2 * Shape<WMC>::STAGE];
-  __shared__ float scales[Shape<WMC>::BM + Shape<WMC>::BN];
-  __shared__ int order[kGather ? 16384 / kReorderBlock : 1];
-  const int w = blockIdx.x;
-  const TileMap tile = map_tile<Shape<WMC>::BM, Shape<WMC>::BN>(M, N, w, w >> 3);
-  if (!tile.valid) return;
-  gemm_fp6_tile<GS, WMC, KS, kPerChannel, kGather, kTiled>(
-      tile, stages, scales, order, Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,
-      out_scale, border);
-}
-
 // LDS of a tile: the stages, alpha of its rows then beta of its columns, the order.
 template <int WMC, int KS, bool kGather>
 struct Lds {
@@ -585,6 +568,21 @@ struct Lds {
   __attribute__((aligned(16))) float scales[Shape<WMC>::BM + Shape<WMC>::BN];
   int order[kGather ? 16384 / kReorderBlock : 1];
 };
+
+template <int GS, int WMC, int KS, bool kPerChannel, bool kGather, bool kTiled>
+__global__ __launch_bounds__(128 * WMC * KS, 2) void gemm_fp6_kernel(
+    const uint8_t* __restrict__ Xe, const float* __restrict__ a_scale,
+    const float* __restrict__ s_group, const uint8_t* __restrict__ Wq,
+    const float* __restrict__ w_scale, int M, int N, int K, uint16_t* __restrict__ Y,
+    float out_scale, const int32_t* __restrict__ border) {
+  __shared__ Lds<WMC, KS, kGather> lds;
+  const int w = blockIdx.x;
+  const TileMap tile = map_tile<Shape<WMC>::BM, Shape<WMC>::BN>(M, N, w, w >> 3);
+  if (!tile.valid) return;
+  gemm_fp6_tile<GS, WMC, KS, kPerChannel, kGather, kTiled>(
+      tile, lds.stages, lds.scales, lds.order, Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,
+      out_scale, border);
+}
 
 // Tiles of 256 x 128 whose last round would leave half of the compute units or more
 // idle: the tiles of the full rounds (workgroups below `full`) as above, each tile after
@@ -642,33 +640,30 @@ hipError_t launch_gemm(bool tail, const uint8_t* Xe, const float* a_scale, const
   const int grid = 8 * ((T + 7) / 8);
   const TailSplit sp = tail ? tail_split(M, N, K) : TailSplit{0, 0};
   const int full = 8 * (sp.per - sp.tail);
-#define RRS_FP6(G_)                                                                        \
-  case G_:                                                                                 \
-    if constexpr (WMC == 4)                                                                \
-      if (sp.tail) {                                                                       \
-        gemm_fp6_tail_kernel<G_ / 32, kPerChannel, kGather, kTiled>                        \
-            <<<full + 16 * sp.tail, 512, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, \
-                                                      K, Y, out_scale, border, full);      \
-        break;                                                                             \
-      }                                                                                    \
-    gemm_fp6_kernel<G_ / 32, WMC, KS, kPerChannel, kGather, kTiled>                        \
-        <<<grid, KS * S::kThreads, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,  \
-                                           out_scale, border);                             \
-    break
+  auto run = [&](auto gs) {
+    constexpr int GS = decltype(gs)::value;
+    if constexpr (WMC == 4)
+      if (sp.tail) {
+        gemm_fp6_tail_kernel<GS, kPerChannel, kGather, kTiled>
+            <<<full + 16 * sp.tail, 512, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,
+                                                      out_scale, border, full);
+        return;
+      }
+    gemm_fp6_kernel<GS, WMC, KS, kPerChannel, kGather, kTiled>
+        <<<grid, KS * S::kThreads, 0, stream>>>(Xe, a_scale, s_group, Wq, w_scale, M, N, K, Y,
+                                                out_scale, border);
+  };
   if constexpr (kPerChannel) {
-    switch (128) {
-      RRS_FP6(128);
-    }
+    run(std::integral_constant<int, 4>{});
   } else {
     switch (g) {
-      RRS_FP6(64);
-      RRS_FP6(128);
-      RRS_FP6(256);
-      RRS_FP6(512);
+      case 64: run(std::integral_constant<int, 2>{}); break;
+      case 128: run(std::integral_constant<int, 4>{}); break;
+      case 256: run(std::integral_constant<int, 8>{}); break;
+      case 512: run(std::integral_constant<int, 16>{}); break;
       default: return hipErrorInvalidValue;
     }
   }
-#undef RRS_FP6
   return hipGetLastError();
 }
 
