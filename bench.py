@@ -11,8 +11,9 @@ region). Inputs are resident in HBM before timing starts.
 
 value = 2*M*N*K / (time per step), effective TOPS of the whole step, where the
 time per step is that of K back-to-back steps between one pair of HIP events.
-The roofline object covers the dominant kernel (the GEMM): its average
-duration is taken from HIP events recorded around it on the launch stream, in
+The roofline object covers the GEMM call (the launch that spreads the token codes,
+and the product), against the dense peak of the matrix instruction that the kernel uses: its
+average duration is taken from HIP events recorded around it on the launch stream, in
 K further steps that also give the breakdown (their per-kernel events add
 their own cost to each step, reported as step_us_with_kernel_events).
 A decode-shaped measurement (M=8, K=8192, N=28672) reports HBM GB/s of the
@@ -38,18 +39,25 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "effective W4A4 TOPS at M=2048,K=4096,N=12288; HBM GB/s at M=8 decode"
-# HBM bytes per launch of the GEMM kernel on this workload, from two rocprofv3
-# --pmc runs (FETCH_SIZE, WRITE_SIZE) scaled by a 256 MiB copy-kernel
-# calibration (profiles/gemm_main_kernel_qkv.md), keyed by the sha1 prefix of
+# HBM bytes per GEMM call on this workload (the token pass and the product), from two
+# rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) scaled by a 256 MiB copy-kernel
+# calibration (profiles/gemm_fp6_kernel_qkv.md), keyed by the sha1 prefix of
 # the kernel source they were measured on. Any other source reports null.
-GEMM_TRAFFIC_BYTES = {"a55e13cd5d24": 159.81e6}
+GEMM_TRAFFIC_BYTES = {"0c1d675f0e10": 203.6e6}
 INT8_MFMA_PEAK_TOPS = 5000.0   # MI355X dense int8 MFMA, 5.0 POP/s
+FP6_MFMA_PEAK_TOPS = 10000.0   # MI355X dense 6-bit MFMA, twice the int8 rate
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
+
+
+def gemm_kernel(rrs, w):
+    """Name of the kernel that rrs.w4a4_gemm takes for workload w, and its MFMA peak."""
+    path = rrs.gemm_path(w.M, w.N, w.K, w.g)
+    return path, FP6_MFMA_PEAK_TOPS if path.startswith("fp6") else INT8_MFMA_PEAK_TOPS
 
 
 def gemm_traffic():
     import hashlib
-    src = os.path.join(ROOT, "paper_2409_20361_amd", "csrc", "rrs_gemm.hip")
+    src = os.path.join(ROOT, "paper_2409_20361_amd", "csrc", "rrs_gemm_fp6.hip")
     with open(src, "rb") as f:
         sha = hashlib.sha1(f.read()).hexdigest()[:12]
     return GEMM_TRAFFIC_BYTES.get(sha)
@@ -331,8 +339,8 @@ def quant_bytes(w):
 
 def config_bench(torch, rrs, synth, names=("gateup", "large"), reps=10):
     """The other prefill configurations, each against its own roofline: the GEMM
-    (int8 MFMA peak) and the quantizer (HBM) timed alone with HIP events, and
-    the whole layer."""
+    (the peak of its matrix instruction; token pass included) and the quantizer
+    (HBM) timed alone with HIP events, and the whole layer."""
     dev = torch.device("cuda:0")
     out = {}
     for name in names:
@@ -369,7 +377,9 @@ def config_bench(torch, rrs, synth, names=("gateup", "large"), reps=10):
             row[key + "_us_median"] = round(t[reps // 2], 2)
         ops = 2.0 * w.M * w.N * w.K
         row["gemm_TOPS"] = round(ops / (row["gemm_us"] * 1e-6) / 1e12, 1)
-        row["gemm_frac_int8_peak"] = round(row["gemm_TOPS"] / INT8_MFMA_PEAK_TOPS, 4)
+        row["gemm_kernel"], peak = gemm_kernel(rrs, w)
+        row["gemm_peak_TOPS"] = peak
+        row["gemm_frac_peak"] = round(row["gemm_TOPS"] / peak, 4)
         row["linear_TOPS"] = round(ops / (row["linear_us"] * 1e-6) / 1e12, 1)
         qb = quant_bytes(w)
         row["quant_GBps"] = round(qb / (row["quant_us"] * 1e-6) / 1e9, 1)
@@ -386,9 +396,8 @@ def few_token_bench(torch, rrs, synth, reps=50):
     with HIP events around 50 back-to-back calls, weights cycling through 4
     copies. At M = 1 and 2 the layer is one launch (every workgroup of the
     GEMM quantizes the rows itself); otherwise the quantizer is one launch
-    with one workgroup per row and the GEMM the weight-streaming kernel up to
-    M = 32 (eight waves from 17 tokens) or the few-token kernel at M = 64.
-    The *_tiled entries
+    with one workgroup per row. gemm_kernel names the GEMM's kernel (the
+    weight-streaming one has eight waves from 17 tokens). The *_tiled entries
     run the same calls on the tiled weight layout."""
     dev = torch.device("cuda:0")
     base = synth.WORKLOADS["decode"]
@@ -421,7 +430,8 @@ def few_token_bench(torch, rrs, synth, reps=50):
             "linear_tiled": lambda i: rrs.linear(X, tiled[i % 4], beta, w.g, workspace=lws,
                                                  out=Y, flags=T),
         }
-        row = {"M": M}
+        row = {"M": M, "gemm_kernel": gemm_kernel(rrs, w)[0],
+               "gemm_kernel_tiled": rrs.gemm_path(M, w.N, w.K, w.g, T)}
         for key, fn in calls.items():
             it = iter(range(1 << 30))
             prewarm(torch, lambda: fn(next(it)), seconds=0.1)
@@ -444,7 +454,7 @@ def few_token_bench(torch, rrs, synth, reps=50):
 def scheme_bench(torch, rrs, reps=30):
     """Kernel comparison of Section 4.5 (Fig. 6): per-channel, Runtime Smooth and
     sub-channel A4W4 on the shared 128 x 128 skeleton, plus the tuned Runtime Smooth
-    kernel, at LLaMA-7B shapes (hidden 4096, sequence length 1024, 1/2/4 sequences).
+    and per-channel calls, at LLaMA-7B shapes (hidden 4096, sequence length 1024, 1/2/4 sequences).
     The GEMMs only read codes and scales, so they run on random packed codes and
     positive scales generated on the GPU."""
     dev = torch.device("cuda:0")
@@ -473,7 +483,9 @@ def scheme_bench(torch, rrs, reps=30):
                 "rrs_tuned": lambda: rrs.w4a4_gemm(Xq, aM, s, Wq, wN, g, out=Y),
                 "per_channel_tuned": lambda: rrs.w4a4_gemm_per_channel(Xq, aM, Wq, wN, out=Y),
             }
-            row = {"proj": proj, "M": M, "N": N, "K": K}
+            row = {"proj": proj, "M": M, "N": N, "K": K,
+                   "rrs_tuned_kernel": rrs.gemm_path(M, N, K, g),
+                   "per_channel_tuned_kernel": rrs.gemm_path(M, N, K, g, per_channel=True)}
             for name, fn in calls.items():
                 for _ in range(5):
                     fn()
@@ -493,7 +505,8 @@ def scheme_bench(torch, rrs, reps=30):
                                              - 1.0, 4)
             rows.append(row)
     return {"skeleton": "128x128 tiles, i8 MFMA (per_channel, runtime_smooth, sub_channel); "
-                        "tuned: the 256x128 main kernel (rrs_tuned, per_channel_tuned)",
+                        "tuned: rrs.w4a4_gemm and rrs.w4a4_gemm_per_channel, on the kernel "
+                        "named in each row",
             "group_size": g, "rows": rows}
 
 
@@ -638,6 +651,7 @@ def main():
     ops = 2.0 * w.M * w.N * w.K
     value = ops / (r["step_ms"] * 1e-3) / 1e12
     gemm_tops = ops / (r["gemm_ms"] * 1e-3) / 1e12
+    path, peak = gemm_kernel(rrs, w)
     out = {
         "metric": METRIC,
         "value": round(value, 2),
@@ -655,11 +669,11 @@ def main():
                    "step": "rrs_rotate_smooth_quant + rrs_w4a4_gemm"},
         "roofline": {
             "bound": "mfma",
-            "kernel": "gemm_main_kernel<4,false,false,false,false> (rrs_w4a4_gemm)",
+            "kernel": f"{path} (rrs.w4a4_gemm, token pass included)",
             "achieved": round(gemm_tops, 2),
-            "peak": INT8_MFMA_PEAK_TOPS,
+            "peak": peak,
             "unit": "TOP/s",
-            "frac": round(gemm_tops / INT8_MFMA_PEAK_TOPS, 4),
+            "frac": round(gemm_tops / peak, 4),
             "traffic": gemm_traffic(),
         },
         "breakdown": {
