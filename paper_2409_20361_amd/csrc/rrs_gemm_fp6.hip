@@ -28,12 +28,13 @@
 // registers and the next tile is staged. While a block's MFMAs run, the vector
 // unit rescales the block before.
 //
-// Measured, GEMM alone, back to back, int8 kernel -> this one (tokens already
-// spread): 2048 x 4096 x 12288, g = 128 111 -> 88 us; 4096 x 4096 x 22016 413 -> 322;
-// 8192 x 8192 x 28672, g = 64 2450 -> 1850; 512 x 8192 x 8192 64 -> 45 (two
-// workgroups of 128 x 128 per compute unit). Spreading 2048 x 4096 tokens takes 4.7
-// us. Counters at 2048 x 4096 x 12288: the MFMA unit is busy 28 % of the clocks,
-// the vector unit 40 %, LDS 34 %; waits for issue and for memory share the rest.
+// Measured, GEMM calls in graph replays, weights cold, row-major, int8 kernel -> this one
+// with the token pass: 2048 x 4096 x 12288, g = 128 115 -> 94 us; 4096 x 4096 x 22016 402 ->
+// 334; 8192 x 8192 x 28672, g = 64 2510 -> 1880; 512 x 8192 x 8192 69 -> 41 (two teams).
+// Spreading 2048 x 4096 tokens takes 4.7 us. Counters at 2048 x 4096 x 12288, of the busy
+// cycles: the MFMA unit 35 %, vector instructions 49 %; of a wave's time a quarter issues
+// vector instructions, 7 % LDS, 28 % waits for data or the barrier, 31 % for its turn to
+// issue.
 // Tried and slower: one wave per SIMD with 128 x 96 (158 us: nothing covers its
 // stalls), four waves per SIMD with 64 x 32 (104: 1.5 times the LDS reads), two
 // register sets for the loads (no gain), fragment pairs as three 128-bit reads
@@ -684,7 +685,7 @@ bool split_teams(int M, int N, int K) {
 // 256 of those (one per unit) 620, a tail of halves 520 and 14 for each of an XCD's tiles
 // (at 16, 1024 x 4096 x 12288, the 128 x 128 tiles stay: per-channel 54.4 us, with the
 // tail 57). Measured: 2048 x K x 12288 (768 / 1536 tiles) 2.34 / 2.67 us per K tile,
-// 512 x 8192 x 8192 (128 / 256 tiles) 51.7 / 45 us in all.
+// 512 x 8192 x 8192 (128 / 256 tiles, one team each) 51.7 / 45 us in all.
 bool small_tiles(int M, int N, int K) {
   const long tn = (N + 127) / 128;
   const long t256 = (long)((M + 255) / 256) * tn, t128 = (long)((M + 127) / 128) * tn;
@@ -698,9 +699,9 @@ bool small_tiles(int M, int N, int K) {
 }  // namespace
 
 // Where the main kernel would serve; with two teams also from 512 tiles of 64 x 64 of
-// the mid-size kernel on (mid-size -> this one, token pass included: 256 x 8192 x
-// 8192, 512 tiles, 33 us both; 640 tiles: 320 x 4096 x 8192 26 -> 22, 128 x 4096 x
-// 20480 27 -> 21; 768 tiles: 384 x 8192 x 8192 46 -> 34, 768 x 16384 x 4096 87 ->
+// the mid-size kernel on (mid-size -> this one, weights in the caches, token pass
+// included: 256 x 8192 x 8192, 512 tiles, 33 us both; 640 tiles: 320 x 4096 x 8192 26 ->
+// 22, 128 x 4096 x 20480 27 -> 21; 768 tiles: 384 x 8192 x 8192 46 -> 34, 768 x 16384 x 4096 87 ->
 // 60; below: 384 x 4096 x 4096, 384 tiles, 18.5 -> 20.7). The scratch stays below
 // 1 GB.
 size_t fp6_scratch_bytes(int M, int N, int K) {

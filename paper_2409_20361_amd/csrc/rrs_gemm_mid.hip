@@ -18,17 +18,18 @@
 // the lane takes two pieces of 8 bytes, an eighth of each group's 32, so that
 // every product stays inside one group.
 //
-// Measured in the kernel alone, back to back, cold weights, g = 128, row-major
-// (tiled), before -> now: 173 x 4096 x 4096 (M x K x N) 35.0 -> 11.1 us (8.7); 64 x
-// 4096 x 4096 12.1 -> 7.1 (5.4); 300 x 8192 x 1024 62.5 -> 13.2 (9.8); 128 x 8192 x
-// 8192 63.9 -> 18.2 (13.9); 100 x 4096 x 12288 35.6 -> 19, where the main kernel
-// served; 49 x 4096 x 22016 22.9 -> 19.0 (20.6 -> 15.0); 32 x 8192 x 28672 29.8 -> 26
-// (28.7 -> 20), where few-token kernels did. At 173 x 4096 x 4096 a wave issues in
-// half of its clocks; four waves beat eight on one tile (11.8 against 12.4 us: the
-// sum of eight takes longer), loads four tiles ahead are slower even with registers
-// for them (12.5 us at one workgroup per compute unit), and so are tiles of 32
-// columns (16.0: the tokens are read twice as often). The last trip's loads past
-// the end cost 6 to 12 % and are left out.
+// Measured in graph replays, cold weights, g = 128, row-major (tiled), the main kernel ->
+// this one: 173 x 4096 x 4096 (M x K x N) 34.5 -> 10.9 us (34.4 -> 8.9); 300 x 8192 x 1024
+// 62.3 -> 13.5 (62.3 -> 10.2); 128 x 8192 x 8192 63.8 -> 21.6 (63.7 -> 16.4); 100 x 4096 x
+// 12288 35.9 -> 19.2 (35.4 -> 15.1); the few-token kernel -> this one: 64 x 4096 x 4096
+// 12.0 -> 7.1 (10.9 -> 5.4); 49 x 4096 x 22016 24.3 -> 20.7 (21.3 -> 16.8); 64 x 8192 x
+// 28672 48.4 -> 44.4 (38.8 -> 35.4); not at K = 8192 with 17 to 32 tokens, row-major (32 x
+// 8192 x 28672 30.4 on the weight stream, 35.8 here: 64 bytes of each of 16 rows per load).
+// At 173 x 4096 x 4096 a wave issues in half of its clocks; four waves beat eight on one
+// tile (11.8 against 12.4 us: the sum of eight takes longer), loads four tiles ahead are
+// slower even with registers for them (12.5 us at one workgroup per compute unit), and so
+// are tiles of 32 columns (16.0: the tokens are read twice as often). The last trip's loads
+// past the end cost 6 to 12 % and are left out.
 //
 // Codes are unpacked into the high nibble of each int8 lane (16 q), the 2^-8
 // folded into the output scale, and a group's accumulators start from the bits

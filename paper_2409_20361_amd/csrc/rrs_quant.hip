@@ -13,11 +13,11 @@
 //      then re-rotates its rows (identical code, identical bits; X mostly
 //      comes from the MALL the second time), takes the per-token maximum of
 //      fl(|y_ij| r_b), and writes alpha_i and the packed INT4 codes.
-// In this file a workgroup holds 1, 2 or 4 teams of 256 threads (K = 16384,
-// 8192, <= 2048: a thread's share of a row stays in registers); each team
-// works on one row at a time. Cross-team and cross-wave reductions go through
-// LDS, no atomics. K = 4096 (and K = 2048 with many rows) takes the
-// one-wave-per-row kernels of rrs_quant_wave.hip instead.
+// In this file a workgroup holds 1, 2 or 4 teams of 256 threads (512 at K =
+// 16384; RowTeams and row_teams say how many); each team works on one row at a
+// time. Cross-team and cross-wave reductions go through LDS, no atomics. K =
+// 4096 (and K = 2048 with many rows) takes the one-wave-per-row kernels of
+// rrs_quant_wave.hip instead.
 #include <type_traits>
 
 #include "rrs_device.h"
@@ -669,8 +669,12 @@ hipError_t launch_block_max_k(const uint16_t* X, int M, bool rot, float* part, i
   return hipGetLastError();
 }
 
-// Runtime reorder, pass 2: quant with one given row of group maxima. (Two teams
-// at K = 8192 and one at 16384: more do not fit in LDS beside the ranking.)
+// Runtime reorder, pass 2: quant with one given row of group maxima. Two teams at K =
+// 8192 and one at 16384, two waves per SIMD: the ranking's tables lie beside the rows, and
+// four and two teams do not fit in LDS with them. The tables are dead once the rows start,
+// so they could share the rows' LDS; that was not tried. Reorder quantizer, before the 32
+// elements per thread -> now: 8192 x 8192 161 -> 150 us, 512 x 8192 22.3 -> 20.0, 2048 x
+// 16384 132 -> 88.
 template <int K>
 hipError_t launch_ordered_k(const uint16_t* X, int M, int g, bool rot, const float* part,
                             int nrows, uint8_t* Xq, float* a_scale, float* s_group,

@@ -37,13 +37,15 @@ constexpr int kMaxPolls = 1 << 18;
 // 16 tokens, 24 MB, reorder: 18.7 us; 96 16.2, 120 15.6, 160 15.6, 240 16.0).
 constexpr int kAheadWgs = 160;
 
-// The layer's GEMM starts when this kernel ends, and until then nearly all compute
-// units and the memory are idle: workgroups past the rows read the first column
-// blocks of its weights, which leaves them in L2 and the memory-side cache. A
-// workgroup takes the blocks of its own index modulo 8, which the GEMM's grid deals to
-// the same XCD. They wait for nothing, so the rows' exchange is as without them. At 8
-// tokens, K = 8192, N = 28672 the layer takes 27.6 us instead of 28.9 (20 us of GEMM, whose
-// 117 MB are at 5.9 TB/s; 24 MB are read here).
+// The layer's GEMM starts when this kernel ends, and until then nearly all compute units
+// and the memory are idle: workgroups past the rows read the first column blocks of its
+// weights, which leaves them in L2 and the memory-side cache. A workgroup takes the
+// blocks of its own index modulo 8, which the grid of the weight-streaming kernel deals
+// to the same XCD (the few-token kernel's workgroups, at K = 16384 with g <= 128, take 2
+// or 4 blocks in a row: there most of them are found in the memory-side cache, not in
+// L2). They wait for nothing, so the rows' exchange is as without them. At 8 tokens, K =
+// 8192, N = 28672 the layer takes 27.6 us instead of 28.9 (20 us of GEMM, whose 117 MB
+// are at 5.9 TB/s; 24 MB are read here).
 template <int K>
 __device__ __forceinline__ void read_ahead(const WeightAhead& ahead, int id, int wgs, int t) {
   constexpr int kLoads = 8 * K / (16 * kRowThreads);  // 16-byte loads per thread and block
@@ -291,8 +293,9 @@ bool quant_rows_fits(int M) { return M >= 1 && M <= kMaxRows; }
 // 27.6 / 27.7; K = 16384, N = 4096, M = 16, 23.6, 22.7 / 22.5 / 21.1. Below, the quantizer
 // is too short: K = 2048, N = 22016, 16 tokens, 15.5, with 16 MB 15.6; three layers of 8
 // tokens whose weights the memory-side cache holds 38.7, with 8 MB 39.8. At K = 1024 the
-// call is bound by the host. The mid-size kernel, whose weights other compute units read,
-// gains nothing (49 x 4096 x 22016 23.2, 24.1 / 24.3 / 24.4).
+// call is bound by the host. From 17 tokens on it was tried with
+// the same deal of blocks only, which is not the mid-size kernel's (an XCD has a run of
+// column tiles there), and gained nothing (49 x 4096 x 22016 23.2, 24.1 / 24.3 / 24.4).
 WeightAhead weight_ahead(const uint8_t* Wq, int M, int N, int K) {
   if (!quant_rows_fits(M) || K < 4096) return {};
   long mb = 16;
