@@ -123,6 +123,26 @@ double both_layouts_us(GemmPath p, GemmCall c) {
   return (path_us(p, c) + other) / 2;
 }
 
+// The share of the main kernel's fitted time that a path has to stay below, where the fits
+// err to one side. Few columns and short K: the main kernel finds the tokens in the caches
+// and is 5 to 8 % faster than fitted, the 6-bit kernels 4 to 13 % slower (7932 x 2048 x 400, g =
+// 256, main 18.7, two teams 23.0 us; 7439 x 2048 x 992, g = 64, 28.0, 256 x 128 tiles 32.3).
+// K = 512: with short groups or per-channel a second round of the mid-size kernel starts with
+// a step that is not in the fit (g = 64, 4587 x 512 x 448, one round, main 11.0, mid-size
+// 11.0; 771 x 512 x 2928, 1.2 rounds, 10.6 / 16.4); with groups of 512, one wave of four has
+// them all, and the fit charges it too much (618 x 512 x 3072, tiled, 9.1 / 6.9). Of 1400 calls
+// with at most 1280 columns or K = 512 95 were more than 4 % slower than on the main kernel,
+// with the shares 16 of 1500.
+double worth_it(GemmPath p, const GemmCall& c) {
+  if (p == GemmPath::kMid) {
+    if (c.K != 512) return 1.0;
+    if (!c.per_channel && c.g >= 256) return c.g == 512 ? 1.04 : 1.0;
+    const int bm = 16 * mid_token_blocks(c.M, c.N, c.K, c.tiled);
+    return (long)ceil_div(c.M, bm) * ceil_div(c.N, 64) > 512 ? 0.8 : 1.0;
+  }
+  return c.N <= 1280 && c.K <= 4096 ? 0.9 : 1.0;
+}
+
 GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
   // Two workgroups of 128 x 128 per compute unit gather row-major weights for twice the
   // tiles, and from K = 4096 the caches no longer hold them: 547 x 8192 x 23696, g = 256,
@@ -137,8 +157,10 @@ GemmPath unless_main_is_faster(GemmPath p, const GemmCall& c) {
   if (gathered && c.K >= gathered && c.reorder && !c.tiled && c.g >= 128) return GemmPath::kMain;
   const bool same_order =
       c.per_channel || p == GemmPath::kFp6Small || p == GemmPath::kFp6Large;
-  const bool main = same_order ? path_us(GemmPath::kMain, c) < path_us(p, c)
-                               : both_layouts_us(GemmPath::kMain, c) < both_layouts_us(p, c);
+  const double share = worth_it(p, c);
+  const bool main = same_order
+                        ? share * path_us(GemmPath::kMain, c) < path_us(p, c)
+                        : share * both_layouts_us(GemmPath::kMain, c) < both_layouts_us(p, c);
   return main ? GemmPath::kMain : p;
 }
 

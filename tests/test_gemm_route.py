@@ -43,8 +43,13 @@ def test_few_tokens(M, K, N, g, tiled, path):
     (547, 8192, 23696, 256, "reorder", False, "main"), (89, 512, 22016, 512, None, False, "main"),
     (134, 8192, 18400, 128, "reorder", False, "main"),
     (134, 8192, 18400, 128, "reorder", True, "fp6_large"),
+    # few columns and short K, where the fits err
+    (7932, 2048, 400, 256, None, False, "main"), (7439, 2048, 992, 64, None, False, "main"),
+    (6884, 2048, 464, 256, None, True, "main"), (771, 512, 2928, 64, None, False, "main"),
+    (258, 512, 7952, 128, None, False, "main"), (1185, 512, 1744, 128, "per_channel", False, "main"),
     # and the others where they are ahead
-    (187, 4096, 17040, 128, "reorder", False, "fp6_large"),
+    (618, 512, 3072, 512, None, True, "mid"), (4000, 8192, 1024, 128, None, False, "fp6_teams"),
+    (5000, 4096, 640, 128, None, False, "fp6_teams"), (187, 4096, 17040, 128, "reorder", False, "fp6_large"),
     (173, 4096, 4096, 128, None, False, "mid"), (512, 8192, 8192, 128, None, False, "fp6_teams"),
     (1024, 4096, 12288, 128, "per_channel", False, "fp6_small"),
     (1500, 4096, 12288, 128, "reorder", False, "fp6_tail"),
