@@ -56,12 +56,14 @@ constexpr int BN = 16 * kCB;
 constexpr int kRedStride = BN + 4;
 constexpr int kMagic = 0x4B400000;  // bits of 1.5 * 2^23
 
-// fp16(a b) with one rounding, as every other kernel stores: the compiler folds their
-// conversion into the product, but not where two halves are packed.
-__device__ __forceinline__ uint16_t half_once(float a, float b) {
+// fp16(a0 b0) and fp16(a1 b1) in one register, with one rounding each, as every other kernel
+// stores: the compiler folds their conversion into the product, but not where two halves are
+// packed. (Packed by shifts and or: 173 x 4096 x 4096 10.85 us, so 10.72.)
+__device__ __forceinline__ uint32_t halves_once(float a0, float b0, float a1, float b1) {
   uint32_t h;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(a), "v"(b));
-  return (uint16_t)h;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(a0), "v"(b0));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(h) : "v"(a1), "v"(b1));
+  return h;
 }
 
 enum Mode { kSmooth, kPerChannel, kPartials };
@@ -313,12 +315,9 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_mid_kernel(
     if (gr < M && gc < N) {
       const float sc = a_scale[gr] * out_scale;
       const v4f bc = *reinterpret_cast<const v4f*>(w_scale + gc);
-      uint16_t h[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        h[e] = half_once(sum[e] * sc, bc[e]);
       *reinterpret_cast<v2u*>(Y + (size_t)gr * N + gc) =
-          v2u{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+          v2u{halves_once(sum[0] * sc, bc[0], sum[1] * sc, bc[1]),
+              halves_once(sum[2] * sc, bc[2], sum[3] * sc, bc[3])};
     }
   }
 }
